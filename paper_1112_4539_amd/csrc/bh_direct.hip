@@ -1,96 +1,197 @@
 // bh_direct.hip -- brute-force O(N^2) sum of Eq. (1) for a list of targets (gfx950).
 //
 // Used as the accuracy judge of the tree walk (the paper compares its tree
-// forces with a brute-force sum, Sec. 5, Eq. (4)) and for the tree versus
-// brute-force crossover.  Sources are staged through LDS in tiles of 256;
-// each thread owns one target and runs over the tile from LDS (broadcast
-// reads).  The FP64 variant keeps the reference order (ascending source
-// index, j == i skipped) and the reference expression, so it reproduces the
-// CPU definition; the FP32 variant uses v_rsq_f32 and FMA.
+// forces with a brute-force sum, Sec. 5, Eq. (4)), for the labels of the
+// learned opening parameter, and for the tree versus brute-force crossover.
+//
+// Bound: VALU issue, about 20 FP64 (14 FP32) instructions and one hardware
+// root per pair.  A workgroup takes 64 / kSub targets; its waves cut the
+// sources into contiguous ranges, and kSub lanes share a target, taking the
+// wave's range in turn.  The partial sums meet in LDS, lanes first, then the
+// waves in order, so that results are the same from run to run.
+//   kSub = 1   many targets: a source is the same for the whole wave, read
+//              four at a time with scalar loads straight into the
+//              instructions' scalar operands (no LDS, no barrier);
+//   kSub > 1   few targets: 64 / kSub of them are enough for a workgroup of up
+//              to 16 waves, so that some hundred targets fill the chip.
+// Four (two) sources are in flight per lane, which hides the chain from r^2
+// through the root to the sums: 13.4 ms for 65,536 targets of 262,147 particles
+// in FP64, 123 cycles per wave and source (7.1 ms, 65 cycles, in FP32).  (One thread per target over LDS tiles of 256
+// sources, with an IEEE root and division per pair in FP64, took 54.1 ms, 494 cycles.)
 #include "bh_internal.h"
 
 namespace bh {
 
-constexpr int kDirectThreads = 256;
+namespace {
 
-template <bool kF64>
-__global__ __launch_bounds__(kDirectThreads) void k_direct(const void* __restrict__ posv, const void* __restrict__ massv,
-                                                           int n, const int64_t* __restrict__ targets, int nt,
-                                                           double eps2, void* __restrict__ accv,
-                                                           void* __restrict__ potv) {
+constexpr int kDirectMaxWaves = 16;
+
+struct DirectArgs {
+  const void* pos;         // [n][3]
+  const void* mass;        // [n]
+  const int64_t* targets;  // [nt]
+  int n, nt;
+  double eps2;
+  void* acc;               // [nt][3]
+  void* pot;               // [nt]
+};
+
+template <typename R>
+struct DirectSum {
+  R ax, ay, az, p;
+  // One source: offset d, mass m (0: adds nothing).  kSoft: eps > 0, so r^2 > 0;
+  // without softening a pair at r = 0 adds nothing.
+  template <bool kSoft>
+  __device__ __forceinline__ void add(R dx, R dy, R dz, R m, R e2) {
+    R ri;
+    if constexpr (std::is_same<R, double>::value) {
+      const double r2 = fma(dz, dz, fma(dy, dy, dx * dx)) + e2;
+      ri = inv_sqrt_f64(r2);
+      if (!kSoft) ri = r2 > 0.0 ? ri : 0.0;
+    } else {
+      const float r2 = fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, e2)));
+      ri = __builtin_amdgcn_rsqf(r2);
+      if (!kSoft) ri = r2 > 0.f ? ri : 0.f;
+    }
+    const R mr = m * ri;
+    const R mr3 = (mr * ri) * ri;
+    ax = fma_(mr3, dx, ax);
+    ay = fma_(mr3, dy, ay);
+    az = fma_(mr3, dz, az);
+    p -= mr;
+  }
+  static __device__ __forceinline__ float fma_(float a, float b, float c) { return fmaf(a, b, c); }
+  static __device__ __forceinline__ double fma_(double a, double b, double c) { return fma(a, b, c); }
+};
+
+#define BH_CONST __attribute__((address_space(4)))
+
+template <bool kF64, bool kSoft, int kSub>
+__global__ __launch_bounds__(64 * kDirectMaxWaves) void k_direct(DirectArgs a) {
   using R = typename std::conditional<kF64, double, float>::type;
-  const R* pos = reinterpret_cast<const R*>(posv);
-  const R* mass = reinterpret_cast<const R*>(massv);
-  __shared__ R sx[kDirectThreads], sy[kDirectThreads], sz[kDirectThreads], sm[kDirectThreads];
-  const int t = blockIdx.x * kDirectThreads + threadIdx.x;
-  const int64_t ti = t < nt ? targets[t] : -1;
-  const bool in_range = ti >= 0 && ti < n;   // an index outside [0, n) yields NaN outputs
-  const bool valid = t < nt && in_range;
-  const int64_t i = valid ? ti : -1;
+  constexpr int kTargets = 64 / kSub;
+  __shared__ double part[kDirectMaxWaves][kTargets][4];
+  const R* pos = reinterpret_cast<const R*>(a.pos);
+  const R* mass = reinterpret_cast<const R*>(a.mass);
+  const int lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  const int slot = lane / kSub, sub = lane % kSub;
+  const int t = blockIdx.x * kTargets + slot;
+  const int64_t ti = t < a.nt ? a.targets[t] : -1;
+  const bool valid = ti >= 0 && ti < a.n;  // an index outside [0, n) yields NaN outputs
+  const int i = valid ? (int)ti : -1;
   R xi = 0, yi = 0, zi = 0;
   if (valid) {
-    xi = pos[3 * i];
-    yi = pos[3 * i + 1];
-    zi = pos[3 * i + 2];
+    xi = pos[3 * (int64_t)i];
+    yi = pos[3 * (int64_t)i + 1];
+    zi = pos[3 * (int64_t)i + 2];
   }
-  R ax = 0, ay = 0, az = 0, p = 0;
-  const R e2 = (R)eps2;
-  for (int base = 0; base < n; base += kDirectThreads) {
-    const int j = base + threadIdx.x;
-    if (j < n) {
-      sx[threadIdx.x] = pos[3 * (int64_t)j];
-      sy[threadIdx.x] = pos[3 * (int64_t)j + 1];
-      sz[threadIdx.x] = pos[3 * (int64_t)j + 2];
-      sm[threadIdx.x] = mass[j];
-    }
-    __syncthreads();
-    const int cnt = min(kDirectThreads, n - base);
-    for (int k = 0; k < cnt; ++k) {
-      if (base + k == i) continue;
-      const R dx = sx[k] - xi, dy = sy[k] - yi, dz = sz[k] - zi;
-      if constexpr (kF64) {
-        const double r2 = dx * dx + dy * dy + dz * dz + e2;
-        if (r2 == 0.0) continue;
-        const double rinv = 1.0 / sqrt(r2);
-        const double mr3 = sm[k] * (rinv * rinv * rinv);
-        ax += mr3 * dx;
-        ay += mr3 * dy;
-        az += mr3 * dz;
-        p -= sm[k] * rinv;
+  const R e2 = (R)a.eps2;
+  DirectSum<R> s{0, 0, 0, 0};
+  const int len = (a.n + nw - 1) / nw;
+  const int j0 = min(w * len, a.n), j1 = min(j0 + len, a.n);
+  if constexpr (kSub == 1) {
+    constexpr int kBatch = 4;
+    const BH_CONST R* ps = (const BH_CONST R*)(uintptr_t)pos;
+    const BH_CONST R* pm = (const BH_CONST R*)(uintptr_t)mass;
+    int j = j0;
+    for (; j + kBatch <= j1; j += kBatch) {
+      R q[3 * kBatch], m[kBatch];
+#pragma unroll
+      for (int k = 0; k < 3 * kBatch; ++k) q[k] = ps[3 * (int64_t)j + k];
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k) m[k] = pm[(int64_t)j + k];
+      // (a batch that holds a lane's own particle is rare: one test per batch)
+      if (ballot((unsigned)(i - j) < (unsigned)kBatch) == 0ull) {
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k)
+          s.template add<kSoft>(q[3 * k] - xi, q[3 * k + 1] - yi, q[3 * k + 2] - zi, m[k], e2);
       } else {
-        const float r2 = fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, e2)));
-        const float ri = (r2 > 0.f) ? __builtin_amdgcn_rsqf(r2) : 0.f;
-        const float mr = sm[k] * ri;
-        const float mr3 = (mr * ri) * ri;
-        ax = fmaf(mr3, dx, ax);
-        ay = fmaf(mr3, dy, ay);
-        az = fmaf(mr3, dz, az);
-        p -= mr;
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k)
+          if (j + k != i) s.template add<kSoft>(q[3 * k] - xi, q[3 * k + 1] - yi, q[3 * k + 2] - zi, m[k], e2);
       }
     }
-    __syncthreads();
+    for (; j < j1; ++j) {
+      const int64_t b = 3 * (int64_t)j;
+      if (j != i) s.template add<kSoft>(ps[b] - xi, ps[b + 1] - yi, ps[b + 2] - zi, pm[j], e2);
+    }
+  } else {
+    constexpr int kBatch = 2;
+    int j = j0 + sub;
+    for (; j + (kBatch - 1) * kSub < j1; j += kBatch * kSub) {
+      R q[3 * kBatch], m[kBatch];
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k) {
+        const int64_t b = (int64_t)j + k * kSub;
+        q[3 * k] = pos[3 * b];
+        q[3 * k + 1] = pos[3 * b + 1];
+        q[3 * k + 2] = pos[3 * b + 2];
+        m[k] = mass[b];
+      }
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k)
+        if (j + k * kSub != i) s.template add<kSoft>(q[3 * k] - xi, q[3 * k + 1] - yi, q[3 * k + 2] - zi, m[k], e2);
+    }
+    for (; j < j1; j += kSub) {
+      const int64_t b = 3 * (int64_t)j;
+      if (j != i) s.template add<kSoft>(pos[b] - xi, pos[b + 1] - yi, pos[b + 2] - zi, mass[j], e2);
+    }
   }
-  if (t >= nt) return;
-  R* acc = reinterpret_cast<R*>(accv);
-  R* pot = reinterpret_cast<R*>(potv);
-  if (!valid) {
-    const R nan = (R)NAN;
-    ax = ay = az = p = nan;
-  }
-  acc[3 * (int64_t)t] = ax;
-  acc[3 * (int64_t)t + 1] = ay;
-  acc[3 * (int64_t)t + 2] = az;
-  pot[t] = p;
+  double v[4] = {(double)s.ax, (double)s.ay, (double)s.az, (double)s.p};
+#pragma unroll
+  for (int o = 1; o < kSub; o <<= 1)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[c] += __shfl_xor(v[c], o, 64);
+  if (sub == 0)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) part[w][slot][c] = v[c];
+  __syncthreads();
+  const int u = threadIdx.x;  // output u / 4 of the workgroup, component u % 4
+  if (u >= 4 * kTargets) return;
+  const int k = u >> 2, c = u & 3, out = blockIdx.x * kTargets + k;
+  if (out >= a.nt) return;
+  double sum = part[0][k][c];
+  for (int q = 1; q < nw; ++q) sum += part[q][k][c];
+  const int64_t to = a.targets[out];
+  if (!(to >= 0 && to < a.n)) sum = NAN;
+  if (c < 3)
+    reinterpret_cast<R*>(a.acc)[3 * (int64_t)out + c] = (R)sum;
+  else
+    reinterpret_cast<R*>(a.pot)[out] = (R)sum;
 }
+
+template <bool kF64, bool kSoft>
+void launch_sub(const DirectArgs& a, int sub, int blocks, int threads, hipStream_t st) {
+  if (sub == 1)
+    k_direct<kF64, kSoft, 1><<<blocks, threads, 0, st>>>(a);
+  else if (sub == 8)
+    k_direct<kF64, kSoft, 8><<<blocks, threads, 0, st>>>(a);
+  else
+    k_direct<kF64, kSoft, 32><<<blocks, threads, 0, st>>>(a);
+}
+
+}  // namespace
 
 hipError_t launch_direct(bool f64, const void* pos, const void* mass, int n, const int64_t* targets, int nt,
                          double eps, void* acc, void* pot, hipStream_t st) {
   if (nt <= 0) return hipSuccess;
-  const int blocks = (nt + kDirectThreads - 1) / kDirectThreads;
+  const DirectArgs a{pos, mass, targets, n, nt, eps * eps, acc, pot};
+  // (FP64, 100,000 sources: one lane per target takes 1.37 ms for up to 16,384
+  // targets, a workgroup on every CU; eight lanes, whose vector loads make a
+  // pair 1.7 times as dear, 0.14 us per target: equal at 9,900.  Below 2048
+  // targets eight lanes no longer fill the chip.)
+  const int sub = nt >= 10240 ? 1 : nt >= 2048 ? 8 : 32;
+  const int blocks = (int)(((int64_t)nt * sub + 63) / 64);
+  // waves: about eight per SIMD on the whole chip (the sum of the targets of a
+  // workgroup uses 4 * 64 / kSub threads), each with 64 sources or more
+  int waves = 4;
+  while (waves < kDirectMaxWaves && (int64_t)blocks * waves < 8192 && (int64_t)waves * 128 <= n) waves *= 2;
+  const bool soft = f64 ? a.eps2 > 0.0 : (float)a.eps2 > 0.f;
   if (f64)
-    k_direct<true><<<blocks, kDirectThreads, 0, st>>>(pos, mass, n, targets, nt, eps * eps, acc, pot);
+    soft ? launch_sub<true, true>(a, sub, blocks, 64 * waves, st) : launch_sub<true, false>(a, sub, blocks, 64 * waves, st);
   else
-    k_direct<false><<<blocks, kDirectThreads, 0, st>>>(pos, mass, n, targets, nt, eps * eps, acc, pot);
+    soft ? launch_sub<false, true>(a, sub, blocks, 64 * waves, st)
+         : launch_sub<false, false>(a, sub, blocks, 64 * waves, st);
   return hipGetLastError();
 }
 

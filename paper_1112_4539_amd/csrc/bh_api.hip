@@ -125,6 +125,9 @@ size_t layout(int64_t n, int64_t K, int prec, char* base, bh::BuildWs* w, int32_
   t.nlev = reinterpret_cast<uint8_t*>(take(nodes));
   t.obkt = reinterpret_cast<int32_t*>(take(4 * bh::kLevels * (size_t)bh::n_chunks((int64_t)N)));
   t.okids = reinterpret_cast<int32_t*>(take(32 * bh::kLevels * (size_t)bh::n_chunks((int64_t)N)));
+  t.anc = K <= bh::kAncClusters
+              ? reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)K * bh::kMaxRuns * bh::kAncSlots))
+              : nullptr;
   // (one spare record past the last: the walk reads the record after its
   // cursor's last position before it tests the loop bound)
   t.wnodes = reinterpret_cast<bh::WalkNode*>(take(sizeof(bh::WalkNode) * (nodes + 1)));
@@ -250,6 +253,20 @@ hipError_t ensure_target_order(const bh_tree* t, hipStream_t st) {
   return hipSuccess;
 }
 
+// Waves that share a group's walk (1: one wave per group).  Measured, build and
+// walk: Plummer 1000 FP32 594 us with one wave and 408 with 16; 4096 FP64 770 and
+// 434; clumpy 30,000 825, 644 with 8 and 752 with 16; Plummer 60,000 at theta 0.35
+// 1639 and 1028 with 4; 100,003 1182 and 1036 with 4.  Beyond that the groups fill
+// the chip by themselves, and waves waiting for the last run of their group cost
+// more than they bring (clumpy 130,000: 1050, 1163 with 4).  In a forest, where
+// the clusters have more runs than one tree of that size, 8 is the better choice
+// (20 clusters, 56,000 particles: 1031, 755 with 4, 681 with 8).
+int split_waves(int64_t n, int64_t n_seg) {
+  const int64_t groups = (n + 63) / 64;
+  if (n > bh::kSplitMaxN) return 1;
+  return groups <= 256 ? 16 : groups <= 512 || n_seg > 1 ? 8 : 4;
+}
+
 int run_walk(const bh_tree* t, double theta, const float* theta_group, double eps, void* acc, void* pot,
              int mode, int32_t* counts, uint64_t* hash, int64_t* lists, int64_t maxlen, int32_t* group_steps,
              hipStream_t st, bool allow_timing = true) {
@@ -323,6 +340,15 @@ int run_walk(const bh_tree* t, double theta, const float* theta_group, double ep
   a.persistent = t->persistent;
   a.targets_per_lane = t->order == 2 ? 1 : t->targets_per_lane;  // (order 2: one target per lane)
   a.queue = t->queue;
+  a.anc = t->w.anc;
+  a.max_runs = t->n_seg == 1 ? bh::walk_segments(t->n) : bh::kMaxRuns;
+  a.split_waves = 1;
+  // Waves per group: the plain launch shape shares a group's walk where the
+  // groups alone would leave SIMDs without waves.
+  if (mode == bh::kWalkForces && a.anc && !a.persistent && a.waves_per_block == 1 && a.lds_share64 == 0 &&
+      a.targets_per_lane == 1) {
+    a.split_waves = split_waves(t->n, t->n_seg);
+  }
   if (a.persistent) {
     a.grid = bh::persistent_grid(t->prec == BH_FP64, t->order == 2 ? (mode | bh::kWalkQuad) : mode, eps * eps > 0.0,
                                  theta_group != nullptr, t->waves_per_block, a.targets_per_lane);

@@ -741,7 +741,9 @@ __global__ __launch_bounds__(256) void k_nodes_internal(const Counts* __restrict
                                                         const int32_t* __restrict__ ustart,
                                                         const uint64_t* __restrict__ ukey, Node* __restrict__ nodes,
                                                         int32_t* __restrict__ nx, uint8_t* __restrict__ nlev,
-                                                        int nmax) {
+                                                        const int64_t* __restrict__ seg_off,
+                                                        const int32_t* __restrict__ croot,
+                                                        int32_t* __restrict__ anc, int nmax) {
   int v = blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= nmax || v >= cnt->n_internal) return;
   const int s = ilevel[v], f = ifirst[v], l = ilast[v];
@@ -764,6 +766,17 @@ __global__ __launch_bounds__(256) void k_nodes_internal(const Counts* __restrict
   nodes[pre] = nd;
   nx[pre] = nd.next;
   nlev[pre] = (uint8_t)s;
+  // the node is an ancestor of the first node of every run that starts inside
+  // its subtree (the walk's runs: walk_segments)
+  if (anc) {
+    const int cl = ucid ? ucid[f] : 0;
+    const int r0 = croot[cl], r1 = croot[cl + 1];
+    const int runs = walk_segments(cluster_size(seg_off, cl, nmax));
+    const int len = max(1, (r1 - r0 + runs - 1) / runs);
+    const int end = min(nd.next, r1) - r0;
+    for (int q = (pre - r0) / len + 1; q < runs && q * len < end; ++q)
+      anc[((int64_t)cl * kMaxRuns + q) * kAncSlots + s] = pre;
+  }
 }
 
 template <typename T4>
@@ -1058,6 +1071,10 @@ static hipError_t build_impl(const T* pos, const T* mass, int n, const BuildWs& 
   // cluster roots for an empty build: every cluster starts and ends at node 0
   k_fill_i32<<<nblk(K + 1, 256), 256, 0, st>>>(w.croot, K + 1, 0);
   if (n == 0) return hipGetLastError();
+  if (w.anc) {
+    const int64_t na = (int64_t)K * kMaxRuns * kAncSlots;
+    k_fill_i32<<<nblk(na, 256), 256, 0, st>>>(w.anc, na, -1);
+  }
   // root cubes
   if (K == 1) {
     const int nbb = w.n_bbox_blocks;
@@ -1126,7 +1143,7 @@ static hipError_t build_impl(const T* pos, const T* mass, int n, const BuildWs& 
   k_croot_final<<<nblk(K + 1, 256), 256, 0, st>>>(K, w.nexcl, w.croot);
   k_nodes_internal<T4><<<nblk(n, 256), 256, 0, st>>>(w.counts, w.cube, ucid, w.ilevel, w.ifirst, w.ilast,
                                                      w.nstart, w.nexcl, w.lmask, w.ustart, w.ukey, w.nodes, w.nx,
-                                                     w.nlev, n);
+                                                     w.nlev, w.seg_off, w.croot, w.anc, n);
   k_nodes_leaf<T4><<<nblk(n, 256), 256, 0, st>>>(w.counts, w.cube, ucid, w.split, w.nstart, w.nexcl, w.ustart,
                                                  reinterpret_cast<const T4*>(w.ps), w.nodes, w.mom, w.nx, w.nlev, n);
   // moments: chunks of the preorder (2n nodes at most), then the straddling

@@ -35,6 +35,28 @@ constexpr int kChunk = 512;
 constexpr int kChunkThreads = 256;  // workgroup of the chunk launches: kChunk / kChunkThreads nodes per thread
 inline int64_t n_chunks(int64_t n) { return (2 * (n > 0 ? n : 1) + kChunk - 1) / kChunk; }
 
+// Runs of a cluster's subtree: a walk sums a target's terms run by run (equally
+// many preorder nodes each) and adds the runs' sums in order.  Several waves can
+// then share a group's walk; the cuts depend on the cluster's size alone, so
+// that a cluster's results do not depend on how it is walked.  Small clusters,
+// whose few groups leave the chip idle, get more runs.
+constexpr int kMaxRuns = 24;
+constexpr int kAncSlots = 24;          // ancestors of a run's first node, by level (kLevels of them used)
+constexpr int kAncClusters = 1024;     // forests of at most this many clusters keep the lists
+constexpr int kMaxSplitWaves = 16;     // waves that share a group
+constexpr int64_t kSplitMaxN = 102400; // largest tree whose groups are shared (1600 groups)
+__host__ __device__ inline int walk_segments(int64_t n) { return n <= 32768 ? 24 : n <= kSplitMaxN ? 16 : 1; }
+// Particles of cluster k (the offsets clamped to [0, n]).
+__host__ __device__ inline int64_t cluster_size(const int64_t* off, int k, int64_t n) {
+  const int64_t b = off[k] < 0 ? 0 : off[k] > n ? n : off[k];
+  const int64_t e = off[k + 1] < b ? b : off[k + 1] > n ? n : off[k + 1];
+  return e - b;
+}
+// Dynamic LDS of the one-wave-per-group walks: the totals of a wave's targets.
+inline size_t walk_lds(int waves_per_block, int targets_per_lane) {
+  return (size_t)waves_per_block * targets_per_lane * 4 * kWave * sizeof(double);
+}
+
 struct BuildWs {
   Cube* cube;               // [K] root cube per cluster
   Counts* counts;
@@ -65,6 +87,7 @@ struct BuildWs {
   uint8_t* nlev;            // [2n] level of every node, for the moment passes
   int32_t* obkt;            // [kLevels][n_chunks] the straddling node of each level and chunk, or -1
   int32_t* okids;           // [kLevels][n_chunks][8] their children in octant order, -1 after the last
+  int32_t* anc;             // [K][kMaxRuns][kAncSlots] ancestors of each run's first node by level, -1 none (null: K > kAncClusters)
   WalkNode* wnodes;         // [2n] walk copy of the nodes for the last uniform theta
   int32_t* horder;          // [n] Morton positions in the Hilbert walk order (filled on demand)
   uint64_t *hkey_a, *hkey_b;  // [n] sort buffers of the Hilbert order (its own: it may run beside the build)
@@ -114,6 +137,7 @@ struct WalkArgs {
   const int32_t* scid;         // Morton position -> cluster (null for a single tree)
   const int32_t* croot;        // [K+1] preorder range of each cluster's subtree
   const int64_t* seg_off;      // [K+1] caller offsets of the clusters (list words are cluster-relative)
+  const int32_t* anc;          // ancestors of the runs' first nodes (BuildWs::anc), may be null
   int n_seg;
   int n;
   double eps2;
@@ -136,6 +160,8 @@ struct WalkArgs {
   int32_t* queue;              // persistent: group counter, zeroed before the launch
   int grid;                    // persistent: workgroups launched
   int targets_per_lane;        // 1 or 2: a wave walks 64 or 128 targets
+  int split_waves;             // > 1: the waves of a workgroup share one group's walk (forces, one target per lane)
+  int max_runs;                // the most runs a cluster of the tree can have
 };
 
 enum WalkMode { kWalkForces = 0, kWalkStats = 1, kWalkDump = 2 };

@@ -79,7 +79,8 @@ int persistent_grid(bool f64, int mode, bool soft, bool group_theta, int waves_p
                                            : walk_f64_stats_fn(m, quad, soft, group_theta, targets_per_lane))
                        : (m == kWalkForces ? walk_f32_forces_fn(quad, soft, group_theta, targets_per_lane)
                                            : walk_f32_stats_fn(m, quad, soft, group_theta, targets_per_lane));
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, waves_per_block * kWave, 0) != hipSuccess) return 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, waves_per_block * kWave,
+                                                   walk_lds(waves_per_block, quad ? 1 : targets_per_lane)) != hipSuccess) return 0;
   return cus * per_cu;
 }
 

@@ -594,12 +594,39 @@ __device__ __forceinline__ void walk_loop_lds(const WalkArgs& a, StepNode<kF64, 
   }
 }
 
+// Partial sums.  A cluster's subtree [r0, r1) is cut into walk_segments(n_k)
+// runs of equally many nodes (bh_internal.h); a target's terms are summed run
+// by run, and the runs' sums are added in order.  The cuts depend on the
+// cluster alone, so one wave that walks the runs one after the other (below)
+// and several that share them (walk_split) give the same bits.
+__device__ __forceinline__ int run_length(int r0, int r1, int runs) { return max(1, (r1 - r0 + runs - 1) / runs); }
+
+// The total of a wave's targets, in LDS between runs ([target of the lane][sum][lane]).
+template <int kT>
+using Totals = double (*)[4][kWave];
+
+template <bool kF64, int kT>
+__device__ __forceinline__ void fold_run(Cursor<kF64, kT>& C, Totals<kT> tot, int lane) {
+#pragma unroll
+  for (int t = 0; t < kT; ++t) {
+    auto& s = C.t[t].acc;
+    tot[t][0][lane] += s.ax;
+    tot[t][1][lane] += s.ay;
+    tot[t][2][lane] += s.az;
+    tot[t][3][lane] += s.p;
+    s.init();
+  }
+}
+
 // The clusters klo..khi of a wave, one subtree after the other; targets of the
 // other clusters stay idle (skip past the subtree).
-template <bool kF64, int kT, int kMode, bool kSoft, bool kPlain, bool kGuard, bool kBucket, bool kLds>
+// kRuns: some cluster's subtree is cut into several runs (else each cluster is
+// one run, and its sums stay in the accumulators).
+template <bool kF64, int kT, int kMode, bool kSoft, bool kPlain, bool kGuard, bool kBucket, bool kLds, bool kRuns>
 __device__ __forceinline__ void walk_clusters(const WalkArgs& a, StepNode<kF64, kPlain> wn, Cursor<kF64, kT>& C,
-                                              uint4 (*pf)[8], const int (&kc)[kT], int klo, int khi) {
+                                              uint4 (*pf)[8], Totals<kT> tot, const int (&kc)[kT], int klo, int khi) {
   const int cap = 2 * a.n;
+  const int lane = __lane_id();
   // (the plain nodes of the FP64 per-group-theta walk keep 64-bit addressing)
   constexpr bool kRaw = kF64 && kPlain;
   const bool off32 = !kRaw && a.n < kOff32MaxN;
@@ -611,32 +638,46 @@ __device__ __forceinline__ void walk_clusters(const WalkArgs& a, StepNode<kF64, 
 #pragma unroll
     for (int t = 0; t < kT; ++t) C.t[t].skip = (C.t[t].i >= 0 && kc[t] == k) ? r0 : 0x7fffffff;
     if (r0 >= r1) continue;
-    if constexpr (kLds && (kMode & kWalkQuad) == 0)
-      walk_loop_lds<kF64, kT, kMode, kSoft, kPlain, kGuard, kBucket>(a, wn, C, pf, r1);
-    else if (off32)
-      walk_loop_scalar<kF64, kT, kMode, kSoft, kPlain, kGuard, kBucket, true>(a, wn, C, r1);
-    else
-      walk_loop_scalar<kF64, kT, kMode, kSoft, kPlain, kGuard, kBucket, false>(a, wn, C, r1);
+    auto loop = [&](int end) {
+      if constexpr (kLds && (kMode & kWalkQuad) == 0)
+        walk_loop_lds<kF64, kT, kMode, kSoft, kPlain, kGuard, kBucket>(a, wn, C, pf, end);
+      else if (off32)
+        walk_loop_scalar<kF64, kT, kMode, kSoft, kPlain, kGuard, kBucket, true>(a, wn, C, end);
+      else
+        walk_loop_scalar<kF64, kT, kMode, kSoft, kPlain, kGuard, kBucket, false>(a, wn, C, end);
+    };
+    if constexpr (!kRuns) {
+      loop(r1);
+    } else {
+      const int runs = uniform(walk_segments(cluster_size(a.seg_off, k, a.n)));
+      const int len = run_length(r0, r1, runs);
+      for (int end = r0; C.c < r1;) {
+        end = min(end + len, r1);
+        if (C.c >= end) continue;
+        loop(end);
+        fold_run<kF64, kT>(C, tot, lane);
+      }
+    }
   }
 }
 
-// The walk of one group of 64 kT targets (one wavefront).
-// kSoft: eps > 0, so r^2 + eps^2 > 0 and the FP32 term needs no zero test.
-// kGroupTheta: theta per walk group (64 targets) instead of one uniform theta
-// (uniform theta walks the copy with S precomputed).
-template <bool kF64, int kT, int kMode, bool kSoft, bool kGroupTheta>
-__device__ __forceinline__ void walk_group(const WalkArgs& a, int group, uint4 (*pf)[8]) {
+// The targets of one group of 64 kT (one wavefront): their state, the clusters
+// they lie in, and whether some theta is above 1.
+template <int kT>
+struct GroupInfo {
+  int kc[kT];     // cluster of the lane's targets
+  int klo, khi;   // clusters of the wave's targets (wave-uniform)
+  bool guard;
+};
+template <bool kF64, int kT, int kMode, bool kGroupTheta>
+__device__ __forceinline__ void load_group(const WalkArgs& a, int group, int lane, Cursor<kF64, kT>& C,
+                                           GroupInfo<kT>& G) {
   using R = typename Cursor<kF64, kT>::R;
   using R4 = typename std::conditional<kF64, double4, float4>::type;
-  constexpr bool kStats = (kMode & 3) != kWalkForces;
-  const int lane = __lane_id();
   const R4* __restrict__ ps = reinterpret_cast<const R4*>(a.ps);
-
-  Cursor<kF64, kT> C;
   C.k = C.kend = 0;
   C.steps = 0;
   bool guard_l = false;
-  int kc[kT];
   int klo = 0x7fffffff, khi = -1;
 #pragma unroll
   for (int t = 0; t < kT; ++t) {
@@ -674,25 +715,53 @@ __device__ __forceinline__ void walk_group(const WalkArgs& a, int group, uint4 (
     guard_l = guard_l || (valid && T.inv_theta < 1.0);
     // Clusters of the wave's targets: a wave usually lies inside one cluster;
     // one that straddles cluster edges walks each cluster's subtree in turn.
-    kc[t] = (valid && a.scid) ? min(max(a.scid[T.i], 0), a.n_seg - 1) : 0;
+    G.kc[t] = (valid && a.scid) ? min(max(a.scid[T.i], 0), a.n_seg - 1) : 0;
     if (valid) {
-      klo = min(klo, kc[t]);
-      khi = max(khi, kc[t]);
+      klo = min(klo, G.kc[t]);
+      khi = max(khi, G.kc[t]);
     }
-    T.node0 = valid ? a.croot[kc[t]] : 0;
-    T.idx0 = valid ? (int)a.seg_off[kc[t]] : 0;
+    T.node0 = valid ? a.croot[G.kc[t]] : 0;
+    T.idx0 = valid ? (int)a.seg_off[G.kc[t]] : 0;
   }
-  const bool guard = ballot(guard_l) != 0ull;
+  G.guard = ballot(guard_l) != 0ull;
   for (int o = 32; o > 0; o >>= 1) {
     klo = min(klo, __shfl_xor(klo, o, 64));
     khi = max(khi, __shfl_xor(khi, o, 64));
   }
-  klo = uniform(klo);
-  khi = uniform(khi);
+  G.klo = uniform(klo);
+  G.khi = uniform(khi);
+}
+
+template <bool kF64, bool kGroupTheta>
+__device__ __forceinline__ StepNode<kF64, kGroupTheta> walk_nodes(const WalkArgs& a) {
   StepNode<kF64, kGroupTheta> wn;
   if constexpr (kGroupTheta && kF64) wn.base = a.nodes;
   else if constexpr (kGroupTheta) wn.base = a.tnodes;
   else wn.base = a.wnodes;
+  return wn;
+}
+
+// The walk of one group of 64 kT targets by one wavefront.
+// kSoft: eps > 0, so r^2 + eps^2 > 0 and the FP32 term needs no zero test.
+// kGroupTheta: theta per walk group (64 targets) instead of one uniform theta
+// (uniform theta walks the copy with S precomputed).
+template <bool kF64, int kT, int kMode, bool kSoft, bool kGroupTheta, bool kRuns>
+__device__ __forceinline__ void walk_group(const WalkArgs& a, int group, uint4 (*pf)[8], Totals<kT> tot) {
+  using R = typename Cursor<kF64, kT>::R;
+  constexpr bool kStats = (kMode & 3) != kWalkForces;
+  const int lane = __lane_id();
+  Cursor<kF64, kT> C;
+  GroupInfo<kT> G;
+  load_group<kF64, kT, kMode, kGroupTheta>(a, group, lane, C, G);
+  if constexpr (kRuns) {
+#pragma unroll
+    for (int t = 0; t < kT; ++t)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) tot[t][c][lane] = 0.0;
+  }
+  const bool guard = G.guard;
+  const int klo = G.klo, khi = G.khi;
+  const StepNode<kF64, kGroupTheta> wn = walk_nodes<kF64, kGroupTheta>(a);
   // Waves split between the two node paths (scalar cache / LDS copies) so
   // that neither the scalar cache nor instruction issue alone sets the pace;
   // the share taking the LDS path is a launch parameter (results identical).
@@ -708,31 +777,22 @@ __device__ __forceinline__ void walk_group(const WalkArgs& a, int group, uint4 (
   // (fewer leaves than particles); without them the step needs no branch for
   // them.
   const bool buckets = uniform(a.cnt->n_unique < a.n ? 1 : 0) != 0;
+#define BH_WALK(guard_, bucket_, lds_) \
+  walk_clusters<kF64, kT, kMode, kSoft, kGroupTheta, guard_, bucket_, lds_, kRuns>(a, wn, C, pf, tot, G.kc, klo, khi)
   if (lds_path) {
     if (buckets) {
-      if (guard)
-        walk_clusters<kF64, kT, kMode, kSoft, kGroupTheta, true, true, true>(a, wn, C, pf, kc, klo, khi);
-      else
-        walk_clusters<kF64, kT, kMode, kSoft, kGroupTheta, false, true, true>(a, wn, C, pf, kc, klo, khi);
+      if (guard) BH_WALK(true, true, true); else BH_WALK(false, true, true);
     } else {
-      if (guard)
-        walk_clusters<kF64, kT, kMode, kSoft, kGroupTheta, true, false, true>(a, wn, C, pf, kc, klo, khi);
-      else
-        walk_clusters<kF64, kT, kMode, kSoft, kGroupTheta, false, false, true>(a, wn, C, pf, kc, klo, khi);
+      if (guard) BH_WALK(true, false, true); else BH_WALK(false, false, true);
     }
   } else {
     if (buckets) {
-      if (guard)
-        walk_clusters<kF64, kT, kMode, kSoft, kGroupTheta, true, true, false>(a, wn, C, pf, kc, klo, khi);
-      else
-        walk_clusters<kF64, kT, kMode, kSoft, kGroupTheta, false, true, false>(a, wn, C, pf, kc, klo, khi);
+      if (guard) BH_WALK(true, true, false); else BH_WALK(false, true, false);
     } else {
-      if (guard)
-        walk_clusters<kF64, kT, kMode, kSoft, kGroupTheta, true, false, false>(a, wn, C, pf, kc, klo, khi);
-      else
-        walk_clusters<kF64, kT, kMode, kSoft, kGroupTheta, false, false, false>(a, wn, C, pf, kc, klo, khi);
+      if (guard) BH_WALK(true, false, false); else BH_WALK(false, false, false);
     }
   }
+#undef BH_WALK
 
 #pragma unroll
   for (int t = 0; t < kT; ++t) {
@@ -742,15 +802,158 @@ __device__ __forceinline__ void walk_group(const WalkArgs& a, int group, uint4 (
     const int o = a.perm[T.i];
     R* accp = reinterpret_cast<R*>(a.acc);
     R* potp = reinterpret_cast<R*>(a.pot);
-    accp[3 * (int64_t)o] = (R)T.acc.ax;
-    accp[3 * (int64_t)o + 1] = (R)T.acc.ay;
-    accp[3 * (int64_t)o + 2] = (R)T.acc.az;
-    potp[o] = (R)T.acc.p;
+    accp[3 * (int64_t)o] = (R)(kRuns ? tot[t][0][lane] : T.acc.ax);
+    accp[3 * (int64_t)o + 1] = (R)(kRuns ? tot[t][1][lane] : T.acc.ay);
+    accp[3 * (int64_t)o + 2] = (R)(kRuns ? tot[t][2][lane] : T.acc.az);
+    potp[o] = (R)(kRuns ? tot[t][3][lane] : T.acc.p);
     if constexpr (kStats) {
       a.counts[2 * (int64_t)o] = T.n_pp;
       a.counts[2 * (int64_t)o + 1] = T.n_pc;
       a.hash[o] = T.h;
     }
+  }
+}
+
+// ---- several waves per group
+// With few groups a walk is bound by the latency of its chain of dependent
+// record loads: 1000 particles are 16 waves of some 900 steps, about 230 ns
+// each.  Here the waves of a workgroup share one group's walk: each takes runs
+// of the subtree (the first by its index, further ones from a counter in LDS),
+// and the runs' sums meet in LDS, added in order.  A wave enters a run at its
+// first node c0 with every target's skip pointer set as a walk from the root
+// would have left it: it tests the ancestors of c0 (listed by the build), and a
+// target that uses one skips its subtree -- the wave whose run holds that
+// ancestor adds the term.  (The walk of 1000 particles took 210 us with one wave
+// per group; split_waves has the other measurements.)
+
+// Skip pointers of the targets at the first node c0 of run s of cluster k.
+template <bool kF64, int kMode, bool kPlain, bool kGuard, bool kOff32>
+__device__ __forceinline__ void enter_run(const WalkArgs& a, StepNode<kF64, kPlain> wn, Target<kF64>& T, int c0,
+                                          int k, int s, int lane) {
+  const int32_t* __restrict__ anc = a.anc + ((int64_t)k * kMaxRuns + s) * kAncSlots;
+  const int mine = lane < kAncSlots ? anc[lane] : -1;
+  uint64_t left = ballot(mine >= 0 && mine < c0);
+  if (!left) return;
+  // (the next ancestor's record is requested before the current one is tested)
+  auto pop = [&]() {
+    const int l = __builtin_ctzll(left);
+    left &= left - 1;
+    return __builtin_amdgcn_readlane(mine, l);
+  };
+  auto rec = wn.template load_at<kOff32>(pop());
+  for (;;) {
+    const auto cur = rec;
+    const bool more = left != 0;
+    if (more) rec = wn.template load_at<kOff32>(pop());
+    using Rec = decltype(rec);
+    const double dx = cur.cx - T.xi, dy = cur.cy - T.yi, dz = cur.cz - T.zi;
+    const double d2 = fma(dz, dz, fma(dy, dy, dx * dx));
+    double S;
+    if constexpr (kPlain) {
+      const double u = fma(cur.l, T.inv_theta, cur.s);
+      S = u * u;
+    } else {
+      S = cur.S;
+    }
+    bool use = d2 > S;
+    if constexpr (kGuard) use = use && (unsigned)(T.i - cur.first) >= (unsigned)cur.count;
+    const int next = std::is_same<Rec, Node>::value ? max(cur.next, c0) : cur.next;
+    if (use) T.skip = max(T.skip, next);
+    if (!more) break;
+  }
+}
+
+// One cluster of a group, its runs shared by the workgroup's waves; part: the
+// runs' sums [run][sum][lane].
+template <bool kF64, int kMode, bool kSoft, bool kPlain, bool kGuard, bool kBucket, bool kOff32>
+__device__ __forceinline__ void split_cluster(const WalkArgs& a, StepNode<kF64, kPlain> wn, Cursor<kF64, 1>& C, int k,
+                                              int r0, int r1, int runs, bool mine, int w,
+                                              int* ticket, double (*part)[4][kWave]) {
+  const int lane = __lane_id();
+  Target<kF64>& T = C.t[0];
+  const int len = run_length(r0, r1, runs);
+  for (int s = w; s < runs;) {
+    const int c0 = r0 + s * len, end = min(c0 + len, r1);
+    if (c0 < end) {
+      T.skip = mine ? r0 : 0x7fffffff;
+      if (s > 0) enter_run<kF64, kMode, kPlain, kGuard, kOff32>(a, wn, T, c0, k, s, lane);
+      C.c = c0;
+      if (ballot(T.skip <= c0) == 0ull) {  // no target is active here: go where the first one is
+        int m = T.skip;
+        for (int o = 32; o > 0; o >>= 1) m = min(m, __shfl_xor(m, o, 64));
+        C.c = uniform(m);
+      }
+      C.k = C.kend = 0;
+      if (C.c < end) {
+        walk_loop_scalar<kF64, 1, kMode, kSoft, kPlain, kGuard, kBucket, kOff32>(a, wn, C, end);
+      }
+    }
+    part[s][0][lane] = T.acc.ax;
+    part[s][1][lane] = T.acc.ay;
+    part[s][2][lane] = T.acc.az;
+    part[s][3][lane] = T.acc.p;
+    T.acc.init();
+    int nx = 0;
+    if (lane == 0) nx = atomicAdd(ticket, 1);
+    s = uniform(nx);
+  }
+}
+
+// One workgroup per group of 64 targets (forces; one target per lane).
+template <bool kF64, int kMode, bool kSoft, bool kGroupTheta>
+__global__ __launch_bounds__(kWave * kMaxSplitWaves) void k_walk_split(WalkArgs a) {
+  using R = typename std::conditional<kF64, double, float>::type;
+  extern __shared__ double dyn_lds[];
+  double (*part)[4][kWave] = reinterpret_cast<double (*)[4][kWave]>(dyn_lds);
+  __shared__ int ticket;
+  const int w = uniform(threadIdx.x >> 6), nw = uniform(blockDim.x >> 6), lane = __lane_id();
+  const int group = remap_block(blockIdx.x, gridDim.x, a.xcd_chunk);
+  Cursor<kF64, 1> C;
+  GroupInfo<1> G;
+  load_group<kF64, 1, kMode, kGroupTheta>(a, group, lane, C, G);
+  Target<kF64>& T = C.t[0];
+  const StepNode<kF64, kGroupTheta> wn = walk_nodes<kF64, kGroupTheta>(a);
+  const bool buckets = uniform(a.cnt->n_unique < a.n ? 1 : 0) != 0;
+  constexpr bool kRaw = kF64 && kGroupTheta;
+  const bool off32 = !kRaw && a.n < kOff32MaxN;
+  for (int k = G.klo; k <= G.khi; ++k) {
+    const int cap = 2 * a.n;
+    const int r0 = min(max(uniform(a.croot[k]), 0), cap);
+    const int r1 = min(max(uniform(a.croot[k + 1]), r0), cap);
+    const int runs = uniform(walk_segments(cluster_size(a.seg_off, k, a.n)));
+    const bool mine = T.i >= 0 && G.kc[0] == k;
+    if (threadIdx.x == 0) ticket = nw;
+    __syncthreads();
+    if (r0 < r1) {
+#define BH_SPLIT(guard_, bucket_, off_) \
+  split_cluster<kF64, kMode, kSoft, kGroupTheta, guard_, bucket_, off_>(a, wn, C, k, r0, r1, runs, mine, w, &ticket, part)
+      if (off32) {
+        if (buckets) {
+          if (G.guard) BH_SPLIT(true, true, !kRaw); else BH_SPLIT(false, true, !kRaw);
+        } else {
+          if (G.guard) BH_SPLIT(true, false, !kRaw); else BH_SPLIT(false, false, !kRaw);
+        }
+      } else {
+        // (trees this large have only the branchless guard and bucket variant)
+        BH_SPLIT(true, true, false);
+      }
+#undef BH_SPLIT
+    }
+    __syncthreads();
+    // the runs' sums in order, one sum per wave
+    if (mine) {
+      const int64_t o = a.perm[T.i];
+      for (int c = w; c < 4; c += nw) {
+        double v = 0.0;
+        if (r0 < r1)
+          for (int s = 0; s < runs; ++s) v += part[s][c][lane];
+        if (c < 3)
+          reinterpret_cast<R*>(a.acc)[3 * o + c] = (R)v;
+        else
+          reinterpret_cast<R*>(a.pot)[o] = (R)v;
+      }
+    }
+    __syncthreads();
   }
 }
 
@@ -761,7 +964,21 @@ __global__ __launch_bounds__(256) void k_walk(WalkArgs a) {
   const int wv = threadIdx.x >> 6;
   const int blk = remap_block(blockIdx.x, gridDim.x, a.xcd_chunk);
   // (a wave past the last target has no valid lane and walks nothing)
-  walk_group<kF64, kT, kMode, kSoft, kGroupTheta>(a, blk * a.waves_per_block + wv, pf_lds[wv]);
+  walk_group<kF64, kT, kMode, kSoft, kGroupTheta, false>(a, blk * a.waves_per_block + wv, pf_lds[wv], nullptr);
+}
+
+// The same where clusters have several runs.  (FP32 with one theta is asked for
+// 8 waves per SIMD: left alone it takes two vector registers too many for that.)
+template <bool kF64, int kT, int kMode, bool kSoft, bool kGroupTheta>
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(!kF64 && kT == 1 && kMode == kWalkForces && !kGroupTheta ? 8 : 1)))
+void k_walk_runs(WalkArgs a) {
+  __shared__ uint4 pf_lds[4][2][8];
+  extern __shared__ double dyn_lds[];  // per wave: the totals of its targets
+  const int wv = threadIdx.x >> 6;
+  const int blk = remap_block(blockIdx.x, gridDim.x, a.xcd_chunk);
+  walk_group<kF64, kT, kMode, kSoft, kGroupTheta, true>(a, blk * a.waves_per_block + wv, pf_lds[wv],
+                                                        reinterpret_cast<Totals<kT>>(dyn_lds) + wv * kT);
 }
 
 // Persistent form: a grid that fits on the chip at once; every wave takes the
@@ -778,6 +995,7 @@ __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(!kF64 && kT == 1 && kMode == kWalkForces && !kGroupTheta ? 8 : 1)))  // (not order 2)
 void k_walk_persistent(WalkArgs a) {
   __shared__ uint4 pf_lds[4][2][8];
+  extern __shared__ double dyn_lds[];
   const int wv = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
   const int groups = (a.n + kT * kWave - 1) / (kT * kWave);
@@ -786,20 +1004,30 @@ void k_walk_persistent(WalkArgs a) {
     if (lane == 0) g = atomicAdd(a.queue, 1);
     g = __shfl(g, 0, 64);
     if (g >= groups) break;
-    walk_group<kF64, kT, kMode, kSoft, kGroupTheta>(a, g, pf_lds[wv]);
+    walk_group<kF64, kT, kMode, kSoft, kGroupTheta, true>(a, g, pf_lds[wv], reinterpret_cast<Totals<kT>>(dyn_lds) + wv * kT);
   }
 }
 
 template <bool kF64, int kT, int kMode, bool kSoft, bool kGroupTheta>
 static hipError_t launch_t(const WalkArgs& a, hipStream_t st) {
   const int groups = (a.n + kT * kWave - 1) / (kT * kWave);
+  if constexpr (kT == 1 && (kMode & 3) == kWalkForces) {
+    if (a.split_waves > 1) {
+      k_walk_split<kF64, kMode, kSoft, kGroupTheta>
+          <<<groups, a.split_waves * kWave, a.max_runs * sizeof(double) * 4 * kWave, st>>>(a);
+      return hipGetLastError();
+    }
+  }
   const int wpb = a.waves_per_block;
   const int blocks = (groups + wpb - 1) / wpb;
+  const size_t lds = walk_lds(wpb, kT);
   if (a.persistent) {
     hipError_t e = fill_i32(a.queue, 1, 0, st);
     if (e != hipSuccess) return e;
-    k_walk_persistent<kF64, kT, kMode, kSoft, kGroupTheta><<<max(1, min(a.grid, blocks)), wpb * kWave, 0, st>>>(a);
-  } else {
+    k_walk_persistent<kF64, kT, kMode, kSoft, kGroupTheta><<<max(1, min(a.grid, blocks)), wpb * kWave, lds, st>>>(a);
+  } else if (a.max_runs > 1 || kT != 1 || (kMode & 3) != kWalkForces) {
+    k_walk_runs<kF64, kT, kMode, kSoft, kGroupTheta><<<blocks, wpb * kWave, lds, st>>>(a);
+  } else if constexpr (kT == 1 && (kMode & 3) == kWalkForces) {
     k_walk<kF64, kT, kMode, kSoft, kGroupTheta><<<blocks, wpb * kWave, 0, st>>>(a);
   }
   return hipGetLastError();

@@ -7,7 +7,7 @@
 // MLP: 8 -> 64 -> 64 -> 1, tanh-form GELU, theta = 0.2 + 0.8 sigmoid(z).
 // Matrix products run on the matrix cores (v_mfma_f32_16x16x32_bf16): bf16
 // operands, FP32 accumulation.  Weights are kept in FP32 (Adam state) and
-// rounded to bf16 copies after every step; biases stay FP32.  One wavefront
+// rounded to bf16 copies after every step; biases stay FP32.  A workgroup
 // handles a tile of 32 rows (two 16-row MFMA blocks), staging activations and
 // their transposes in LDS so that every operand fragment is one 16-byte read.
 #include "bh_internal.h"
@@ -229,7 +229,14 @@ struct MlpArgs {
   const float* norm;     // [16]: mu[8], 1/sd[8]
 };
 
-// LDS of one wavefront: a 32-row tile, row-major and transposed copies.
+// A workgroup of four waves takes a tile of 32 rows, each wave 16 of the 64
+// hidden columns: a tile is a serial chain of small matrix products and about
+// 4000 tanh, and a batch has few tiles (128 at 4096 rows), so what it costs is
+// the length of that chain.  (With one wave per tile the gradient of 4096 rows
+// took 25 us and inference of 16,384 rows 16 us.)
+constexpr int kMlpWaves = 4;
+
+// LDS of one workgroup: a 32-row tile, row-major and transposed copies.
 struct alignas(16) TileLds {
   uint16_t xb[32][8];
   uint16_t xT[8][32];
@@ -245,46 +252,46 @@ struct alignas(16) TileLds {
   float tgt[32];
 };
 
-// Normalised bf16 inputs of the tile's rows (lanes 0..31 take one row each;
-// rows past `rows` are zero).
+// Normalised bf16 inputs of the tile's rows, one feature per thread (rows past
+// `rows` are zero).
 template <bool kT>
 __device__ __forceinline__ void load_rows(const MlpArgs& w, const float* __restrict__ X, int64_t rows, int64_t row0,
-                                          const int32_t* __restrict__ idx, TileLds& s, int lane,
-                                          const float* __restrict__ T) {
-  if (lane < 32) {
-    const int64_t row = row0 + lane;
-    const bool valid = row < rows;
-    const int64_t src = valid ? (idx ? (int64_t)idx[row] : row) : 0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const float v = valid ? (X[8 * src + k] - w.norm[k]) * w.norm[8 + k] : 0.0f;
-      const uint16_t hb = valid ? to_bf16(v) : (uint16_t)0;
-      s.xb[lane][k] = hb;
-      if constexpr (kT) s.xT[k][lane] = hb;
-    }
-    if constexpr (kT) s.tgt[lane] = valid ? T[src] : 0.0f;
+                                          const int32_t* __restrict__ idx, TileLds& s, const float* __restrict__ T) {
+  const int j = threadIdx.x >> 3, k = threadIdx.x & 7;
+  const int64_t row = row0 + j;
+  const bool valid = row < rows;
+  const int64_t src = valid ? (idx ? (int64_t)idx[row] : row) : 0;
+  const float v = valid ? (X[8 * src + k] - w.norm[k]) * w.norm[8 + k] : 0.0f;
+  const uint16_t hb = valid ? to_bf16(v) : (uint16_t)0;
+  s.xb[j][k] = hb;
+  if constexpr (kT) {
+    s.xT[k][j] = hb;
+    if (k == 0) s.tgt[j] = valid ? T[src] : 0.0f;
   }
 }
 
-// Forward pass of rows 16h..16h+15 of the tile: hidden states (and, for the
-// gradient pass, their transposes and the GELU slopes) to LDS; z in the lanes
-// with l%16 == 0 (rows 16h + 4(l/16) + i).
+// The hidden layers of the tile's columns 16q..16q+15: states (and, for the
+// gradient pass, their transposes and the GELU slopes) to LDS.  Ends with a
+// barrier.
 template <bool kT>
-__device__ __forceinline__ void fwd_half(const MlpArgs& w, TileLds& s, int h, int lane, f32x4& z) {
+__device__ __forceinline__ void fwd_hidden(const MlpArgs& w, TileLds& s, int q, int lane) {
   const int r = lane & 15, g = lane >> 4;
+  const int col = 16 * q + r;
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
   // layer 1: K = 8 features, padded to 32 with zeros
-  const bf16x8 ax = g == 0 ? frag(&s.xb[16 * h + r][0]) : zero8();
+  const bf16x8 bw1 = g == 0 ? frag(w.wb + kMlpW1b + col * 8) : zero8();
+  const float bias1 = w.P[kMlpB1 + col];
+  const bf16x8 bw2a = frag(w.wb + kMlpW2b + col * 64 + 8 * g);
+  const bf16x8 bw2b = frag(w.wb + kMlpW2b + col * 64 + 32 + 8 * g);
+  const float bias2 = w.P[kMlpB2 + col];
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
-    const bf16x8 bw = g == 0 ? frag(w.wb + kMlpW1b + (16 * nt + r) * 8) : zero8();
-    const f32x4 d = mma(ax, bw, zero);
-    const int col = 16 * nt + r;
-    const float bias = w.P[kMlpB1 + col];
+  for (int h = 0; h < 2; ++h) {
+    const bf16x8 ax = g == 0 ? frag(&s.xb[16 * h + r][0]) : zero8();
+    const f32x4 d = mma(ax, bw1, zero);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int row = 16 * h + 4 * g + i;
-      const float v = d[i] + bias;
+      const float v = d[i] + bias1;
       const uint16_t hb = to_bf16(gelu(v));
       s.h1[row][col] = hb;
       if constexpr (kT) {
@@ -296,49 +303,52 @@ __device__ __forceinline__ void fwd_half(const MlpArgs& w, TileLds& s, int h, in
   __syncthreads();
   // layer 2: K = 64
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
-    f32x4 d = zero;
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-      d = mma(frag(&s.h1[16 * h + r][32 * ks + 8 * g]), frag(w.wb + kMlpW2b + (16 * nt + r) * 64 + 32 * ks + 8 * g), d);
-    const int col = 16 * nt + r;
-    const float bias = w.P[kMlpB2 + col];
+  for (int h = 0; h < 2; ++h) {
+    f32x4 d = mma(frag(&s.h1[16 * h + r][8 * g]), bw2a, zero);
+    d = mma(frag(&s.h1[16 * h + r][32 + 8 * g]), bw2b, d);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float v = d[i] + bias;
+      const float v = d[i] + bias2;
       s.h2[16 * h + 4 * g + i][col] = to_bf16(gelu(v));
       if constexpr (kT) s.gd2[16 * h + 4 * g + i][col] = gelu_grad(v);
     }
   }
   __syncthreads();
-  // layer 3: one output column (B is zero outside column 0)
-  f32x4 d = zero;
+}
+
+// The output layer of rows 16h..16h+15: z in the lanes with l%16 == 0 (rows
+// 16h + 4(l/16) + i).
+__device__ __forceinline__ f32x4 fwd_out(const MlpArgs& w, const TileLds& s, int h, int lane) {
+  const int r = lane & 15, g = lane >> 4;
+  // one output column (B is zero outside column 0)
+  f32x4 d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks)
     d = mma(frag(&s.h2[16 * h + r][32 * ks + 8 * g]), r == 0 ? frag(w.wb + kMlpw3b + 32 * ks + 8 * g) : zero8(), d);
   const float b3 = w.P[kMlpB3];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) z[i] = d[i] + b3;
+  for (int i = 0; i < 4; ++i) d[i] += b3;
+  return d;
 }
 
 // theta for every row of X: 0.2 + 0.8 sigmoid(z), times alpha, at most `cap`;
 // a non-finite result is replaced by `fallback`.
-__global__ __launch_bounds__(64) void k_mlp_infer(MlpArgs w, const float* __restrict__ X, int64_t rows, float alpha,
-                                                  float fallback, float cap, float* __restrict__ theta) {
+__global__ __launch_bounds__(64 * kMlpWaves) void k_mlp_infer(MlpArgs w, const float* __restrict__ X, int64_t rows,
+                                                              float alpha, float fallback, float cap,
+                                                              float* __restrict__ theta) {
   __shared__ TileLds s;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63, q = uniform(threadIdx.x >> 6);
   const int r = lane & 15, g = lane >> 4;
   for (int64_t tile = blockIdx.x; tile * 32 < rows; tile += gridDim.x) {
-    load_rows<false>(w, X, rows, tile * 32, nullptr, s, lane, nullptr);
+    load_rows<false>(w, X, rows, tile * 32, nullptr, s, nullptr);
     __syncthreads();
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      f32x4 z;
-      fwd_half<false>(w, s, h, lane, z);
+    fwd_hidden<false>(w, s, q, lane);
+    if (q < 2) {
+      const f32x4 z = fwd_out(w, s, q, lane);
       if (r == 0) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const int64_t row = tile * 32 + 16 * h + 4 * g + i;
+          const int64_t row = tile * 32 + 16 * q + 4 * g + i;
           if (row < rows) {
             float th = (0.2f + 0.8f / (1.0f + expf(-z[i]))) * alpha;
             if (!isfinite(th)) th = fallback;
@@ -346,145 +356,144 @@ __global__ __launch_bounds__(64) void k_mlp_infer(MlpArgs w, const float* __rest
           }
         }
       }
-      __syncthreads();
     }
+    __syncthreads();
   }
 }
 
 // Gradient of the batch loss mean((sigmoid(z) - t)^2) over the rows idx[0..B):
 // every workgroup accumulates its tiles' contributions (weight gradients in
-// MFMA accumulators) and writes one partial vector; k_mlp_reduce sums them in
-// a fixed order.
-__global__ __launch_bounds__(64) void k_mlp_grad(MlpArgs w, const float* __restrict__ X, const float* __restrict__ T,
-                                                 const int32_t* __restrict__ idx, int batch,
-                                                 float* __restrict__ partial) {
+// MFMA accumulators, wave q those of rows 16q..16q+15 of W1 and W2) and writes
+// one partial vector; k_mlp_reduce sums them in a fixed order.
+__global__ __launch_bounds__(64 * kMlpWaves) void k_mlp_grad(MlpArgs w, const float* __restrict__ X,
+                                                             const float* __restrict__ T,
+                                                             const int32_t* __restrict__ idx, int batch,
+                                                             float* __restrict__ partial) {
   __shared__ TileLds s;
-  const int lane = threadIdx.x;
+  __shared__ float loss2[2];
+  const int lane = threadIdx.x & 63, q = uniform(threadIdx.x >> 6);
   const int r = lane & 15, g = lane >> 4;
+  const int col = 16 * q + r;
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-  f32x4 gW2[4][4], gW1[4];
+  f32x4 gW2[4], gW1 = zero;
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    gW1[a] = zero;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) gW2[a][b] = zero;
-  }
-  float gb1[4] = {0.f, 0.f, 0.f, 0.f}, gb2[4] = {0.f, 0.f, 0.f, 0.f};
-  float gw3 = 0.f, gb3 = 0.f, loss = 0.f;
+  for (int b = 0; b < 4; ++b) gW2[b] = zero;
+  float gb1 = 0.f, gb2 = 0.f, gw3 = 0.f, gb3 = 0.f, loss = 0.f;
   const float scale = 2.0f / (float)batch;
+  const float w3c = from_bf16(w.wb[kMlpw3b + col]);
   for (int64_t tile = blockIdx.x; tile * 32 < batch; tile += gridDim.x) {
-    load_rows<true>(w, X, batch, tile * 32, idx, s, lane, T);
+    load_rows<true>(w, X, batch, tile * 32, idx, s, T);
     __syncthreads();
-    f32x4 z[2];
-    fwd_half<true>(w, s, 0, lane, z[0]);
-    fwd_half<true>(w, s, 1, lane, z[1]);
-    // output error
-    if (r == 0) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
+    fwd_hidden<true>(w, s, q, lane);
+    // output error, half a tile per wave
+    if (q < 2) {
+      const f32x4 z = fwd_out(w, s, q, lane);
+      if (r == 0) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const int row = 16 * h + 4 * g + i;
+          const int row = 16 * q + 4 * g + i;
           const bool valid = tile * 32 + row < batch;
-          const float y = 1.0f / (1.0f + expf(-z[h][i]));
+          const float y = 1.0f / (1.0f + expf(-z[i]));
           const float e = y - s.tgt[row];
           s.dz[row] = valid ? scale * e * y * (1.0f - y) : 0.0f;
           loss += valid ? e * e : 0.0f;
         }
+      }
     }
     __syncthreads();
-    // last layer: lane l owns w3[l]
-    for (int row = 0; row < 32; ++row) gw3 += s.dz[row] * from_bf16(s.h2[row][lane]);
-    if (lane == 0)
-      for (int row = 0; row < 32; ++row) gb3 += s.dz[row];
+    // last layer: lane l of wave 2 owns w3[l], wave 3 the bias
+    if (q == 2) {
+      for (int row = 0; row < 32; ++row) gw3 += s.dz[row] * from_bf16(s.h2[row][lane]);
+    } else if (q == 3) {
+      gb3 += lane < 32 ? s.dz[lane] : 0.0f;
+    }
     // error of the second hidden layer
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt) {
-        const int col = 16 * nt + r;
-        const float w3c = from_bf16(w.wb[kMlpw3b + col]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int row = 16 * h + 4 * g + i;
-          const float dp = s.dz[row] * w3c * s.gd2[row][col];
-          gb2[nt] += dp;
-          const uint16_t hb = to_bf16(dp);
-          s.dp2[row][col] = hb;
-          s.dp2T[col][row] = hb;
-        }
+      for (int i = 0; i < 4; ++i) {
+        const int row = 16 * h + 4 * g + i;
+        const float dp = s.dz[row] * w3c * s.gd2[row][col];
+        gb2 += dp;
+        const uint16_t hb = to_bf16(dp);
+        s.dp2[row][col] = hb;
+        s.dp2T[col][row] = hb;
       }
     __syncthreads();
     // error of the first hidden layer: dh1 = bf16(dpre2) W2
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < 2; ++h) {
+      f32x4 d = zero;
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt) {
-        f32x4 d = zero;
+      for (int ks = 0; ks < 2; ++ks)
+        d = mma(frag(&s.dp2[16 * h + r][32 * ks + 8 * g]), frag(w.wb + kMlpW2Tb + col * 64 + 32 * ks + 8 * g), d);
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-          d = mma(frag(&s.dp2[16 * h + r][32 * ks + 8 * g]),
-                  frag(w.wb + kMlpW2Tb + (16 * nt + r) * 64 + 32 * ks + 8 * g), d);
-        const int col = 16 * nt + r;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int row = 16 * h + 4 * g + i;
-          const float dp = d[i] * s.gd1[row][col];
-          gb1[nt] += dp;
-          s.dp1T[col][row] = to_bf16(dp);
-        }
+      for (int i = 0; i < 4; ++i) {
+        const int row = 16 * h + 4 * g + i;
+        const float dp = d[i] * s.gd1[row][col];
+        gb1 += dp;
+        s.dp1T[col][row] = to_bf16(dp);
       }
+    }
     // dW2 += bf16(dpre2)^T h1 (contraction over the tile's 32 rows)
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt)
-        gW2[mt][nt] = mma(frag(&s.dp2T[16 * mt + r][8 * g]), frag(&s.h1T[16 * nt + r][8 * g]), gW2[mt][nt]);
+    for (int nt = 0; nt < 4; ++nt)
+      gW2[nt] = mma(frag(&s.dp2T[col][8 * g]), frag(&s.h1T[16 * nt + r][8 * g]), gW2[nt]);
     __syncthreads();
     // dW1 += bf16(dpre1)^T x'
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-      gW1[mt] = mma(frag(&s.dp1T[16 * mt + r][8 * g]), r < 8 ? frag(&s.xT[r][8 * g]) : zero8(), gW1[mt]);
+    gW1 = mma(frag(&s.dp1T[col][8 * g]), r < 8 ? frag(&s.xT[r][8 * g]) : zero8(), gW1);
     __syncthreads();
   }
   // this workgroup's partial gradient
   float* out = partial + (int64_t)blockIdx.x * kMlpGradLen;
 #pragma unroll
-  for (int mt = 0; mt < 4; ++mt)
+  for (int i = 0; i < 4; ++i) {
+    const int o = 16 * q + 4 * g + i;
+    if (r < 8) out[kMlpW1 + o * 8 + r] = gW1[i];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int o = 16 * mt + 4 * g + i;
-      if (r < 8) out[kMlpW1 + o * 8 + r] = gW1[mt][i];
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt) out[kMlpW2 + o * 64 + 16 * nt + r] = gW2[mt][nt][i];
-    }
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
-    float b1 = gb1[nt], b2 = gb2[nt];
-    b1 += __shfl_xor(b1, 16, 64);
-    b1 += __shfl_xor(b1, 32, 64);
-    b2 += __shfl_xor(b2, 16, 64);
-    b2 += __shfl_xor(b2, 32, 64);
-    if (g == 0) {
-      out[kMlpB1 + 16 * nt + r] = b1;
-      out[kMlpB2 + 16 * nt + r] = b2;
-    }
+    for (int nt = 0; nt < 4; ++nt) out[kMlpW2 + o * 64 + 16 * nt + r] = gW2[nt][i];
   }
-  out[kMlpw3 + lane] = gw3;
+  gb1 += __shfl_xor(gb1, 16, 64);
+  gb1 += __shfl_xor(gb1, 32, 64);
+  gb2 += __shfl_xor(gb2, 16, 64);
+  gb2 += __shfl_xor(gb2, 32, 64);
+  if (g == 0) {
+    out[kMlpB1 + col] = gb1;
+    out[kMlpB2 + col] = gb2;
+  }
+  if (q == 2) out[kMlpw3 + lane] = gw3;
+  if (q == 3) {
+    for (int o = 1; o < 32; o <<= 1) gb3 += __shfl_xor(gb3, o, 64);
+    if (lane == 0) out[kMlpB3] = gb3;
+  }
   loss += __shfl_xor(loss, 16, 64);
   loss += __shfl_xor(loss, 32, 64);
-  if (lane == 0) {
-    out[kMlpB3] = gb3;
-    out[kMlpParams] = loss;
-  }
+  if (q < 2 && lane == 0) loss2[q] = loss;
+  __syncthreads();
+  if (threadIdx.x == 0) out[kMlpParams] = loss2[0] + loss2[1];
 }
 
-__global__ __launch_bounds__(256) void k_mlp_reduce(const float* __restrict__ partial, int nparts, int batch,
-                                                    float* __restrict__ grad) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= kMlpGradLen) return;
+// The partial vectors' sum, FP64, in a fixed order: a workgroup takes 32
+// parameters, eight threads each an eighth of the vectors.  (One thread per
+// parameter read 128 vectors one after the other on 19 workgroups: 32 us.)
+constexpr int kReduceParams = 32, kReduceSlices = 8;
+__global__ __launch_bounds__(kReduceParams * kReduceSlices) void k_mlp_reduce(const float* __restrict__ partial,
+                                                                              int nparts, int batch,
+                                                                              float* __restrict__ grad) {
+  __shared__ double red[kReduceSlices][kReduceParams];
+  const int c = threadIdx.x % kReduceParams, sl = threadIdx.x / kReduceParams;
+  const int p = blockIdx.x * kReduceParams + c;
   double s = 0.0;
-  for (int b = 0; b < nparts; ++b) s += (double)partial[(int64_t)b * kMlpGradLen + p];
+  if (p < kMlpGradLen) {
+    const int per = (nparts + kReduceSlices - 1) / kReduceSlices;
+    const int b1 = min((sl + 1) * per, nparts);
+#pragma unroll 8
+    for (int b = sl * per; b < b1; ++b) s += (double)partial[(int64_t)b * kMlpGradLen + p];
+  }
+  red[sl][c] = s;
+  __syncthreads();
+  if (sl != 0 || p >= kMlpGradLen) return;
+  for (int k = 1; k < kReduceSlices; ++k) s += red[k][c];
   grad[p] = (float)(p == kMlpParams ? s / (double)batch : s);
 }
 
@@ -536,7 +545,7 @@ hipError_t launch_mlp_infer(const float* P, const uint16_t* wb, const float* nor
   MlpArgs w{P, wb, norm};
   const int64_t tiles = (rows + 31) / 32;
   const int grid = (int)(tiles < 4096 ? tiles : 4096);
-  k_mlp_infer<<<grid, 64, 0, st>>>(w, X, rows, alpha, fallback, cap, theta);
+  k_mlp_infer<<<grid, 64 * kMlpWaves, 0, st>>>(w, X, rows, alpha, fallback, cap, theta);
   return hipGetLastError();
 }
 
@@ -549,8 +558,8 @@ hipError_t launch_mlp_grad(const float* P, const uint16_t* wb, const float* norm
                            const int32_t* idx, int batch, float* partial, float* grad, hipStream_t st) {
   MlpArgs w{P, wb, norm};
   const int parts = mlp_grad_parts(batch);
-  k_mlp_grad<<<parts, 64, 0, st>>>(w, X, T, idx, batch, partial);
-  k_mlp_reduce<<<blocks(kMlpGradLen, 256), 256, 0, st>>>(partial, parts, batch, grad);
+  k_mlp_grad<<<parts, 64 * kMlpWaves, 0, st>>>(w, X, T, idx, batch, partial);
+  k_mlp_reduce<<<blocks(kMlpGradLen, kReduceParams), kReduceParams * kReduceSlices, 0, st>>>(partial, parts, batch, grad);
   return hipGetLastError();
 }
 

@@ -216,6 +216,16 @@ hipError_t enqueue_build(const bh_tree* t, hipStream_t st, bool may_fork = true)
   t->horder_ready = false;
   t->quad_ready = false;
   t->rank_ready = false;
+  if (t->n_seg == 1 && t->n >= 1 && t->n <= bh::kSmallBuild) {
+    const int n = (int)t->n;
+    hipError_t e = t->prec == BH_FP64
+                       ? bh::build_small_f64(static_cast<const double*>(t->pos), static_cast<const double*>(t->mass), n,
+                                             t->w, st)
+                       : bh::build_small_f32(static_cast<const float*>(t->pos), static_cast<const float*>(t->mass), n,
+                                             t->w, st);
+    if (e == hipSuccess) t->horder_ready = true;
+    return e;
+  }
   bool fork = may_fork && t->target_order == 2 && t->n > 0;
   if (fork) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;

@@ -349,6 +349,20 @@ __device__ __forceinline__ uint32_t compact3(uint64_t v) {
 // bits with x as the most significant bit of each triplet, so the octant of a
 // child is 4*bx + 2*by + bz and key order is depth-first (Morton) order.
 template <typename T>
+__device__ __forceinline__ uint64_t morton_key(const Cube& cube, const T* __restrict__ pos, int i) {
+  const double sc = cube.scale;
+  uint64_t q[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    double t = floor(((double)pos[3 * (int64_t)i + d] - cube.lo[d]) * sc);
+    if (!(t >= 0.0)) t = 0.0;  // also maps a non-finite input to 0 (flagged by bbox)
+    if (t > (double)(kGrid - 1)) t = (double)(kGrid - 1);
+    q[d] = (uint64_t)t;
+  }
+  return (spread3(q[0]) << 2) | (spread3(q[1]) << 1) | spread3(q[2]);
+}
+
+template <typename T>
 __global__ __launch_bounds__(256) void k_keys(const T* __restrict__ pos, int n, const Cube* __restrict__ cubes,
                                               const int64_t* __restrict__ off, int K, int32_t* __restrict__ seg,
                                               uint64_t* __restrict__ keys, int32_t* __restrict__ idx) {
@@ -356,17 +370,7 @@ __global__ __launch_bounds__(256) void k_keys(const T* __restrict__ pos, int n, 
   if (i >= n) return;
   const int k = K > 1 ? seg_of(off, K, i) : 0;
   if (seg) seg[i] = k;
-  const Cube* cube = cubes + k;
-  const double sc = cube->scale;
-  uint64_t q[3];
-#pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    double t = floor(((double)pos[3 * (int64_t)i + d] - cube->lo[d]) * sc);
-    if (!(t >= 0.0)) t = 0.0;  // also maps a non-finite input to 0 (flagged by bbox)
-    if (t > (double)(kGrid - 1)) t = (double)(kGrid - 1);
-    q[d] = (uint64_t)t;
-  }
-  keys[i] = (spread3(q[0]) << 2) | (spread3(q[1]) << 1) | spread3(q[2]);
+  keys[i] = morton_key(cubes[k], pos, i);
   idx[i] = i;
 }
 
@@ -620,6 +624,50 @@ __device__ __forceinline__ bool same_cell(uint64_t a, uint64_t b, int level) {
   return level == 0 || ((a ^ b) >> (63 - 3 * level)) == 0ull;
 }
 
+// Key range [f, l] of the cell of level s that separates the adjacent unique
+// keys j (kj) and j + 1 (kj1), by galloping and binary search (keys are sorted,
+// so a range shares a prefix iff its ends do); true if j | j + 1 is the cell's
+// first child boundary.  key(m): unique key m; mine(m): key m is of j's cluster.
+template <typename Key, typename Mine>
+__device__ __forceinline__ bool cell_range(int j, int U, int s, uint64_t kj, uint64_t kj1, Key&& key, Mine&& mine,
+                                           int& f_out, int& l_out) {
+  auto in_cell = [&](int m, uint64_t ref) { return mine(m) && same_cell(key(m), ref, s); };
+  // first key of the cell: smallest f <= j with same_cell(key(f), kj, s)
+  int lo = j, step = 1;
+  while (true) {
+    int cand = j - step;
+    if (cand < 0 || !in_cell(cand, kj)) break;
+    lo = cand;
+    step <<= 1;
+  }
+  int hi_bad = j - step;  // < 0 or outside the cell
+  int a = hi_bad, b = lo;  // invariant: a outside (or -1), b inside
+  if (a < -1) a = -1;
+  while (b - a > 1) {
+    int m = a + (b - a) / 2;
+    if (in_cell(m, kj)) b = m; else a = m;
+  }
+  const int f = b;
+  // last key of the cell: largest l >= j+1 with same_cell(key(l), kj1, s)
+  int up = j + 1;
+  step = 1;
+  while (true) {
+    int cand = j + 1 + step;
+    if (cand >= U || !in_cell(cand, kj1)) break;
+    up = cand;
+    step <<= 1;
+  }
+  int c = up, d = j + 1 + step;  // c inside, d outside (or U)
+  if (d > U) d = U;
+  while (d - c > 1) {
+    int m = c + (d - c) / 2;
+    if (in_cell(m, kj1)) c = m; else d = m;
+  }
+  f_out = f;
+  l_out = c;
+  return (f == j) || (s < kLevels - 1 && same_cell(key(f), kj, s + 1));
+}
+
 // For each pair of adjacent unique keys j, j+1 with split level s, the
 // oct-tree cell (s, prefix) exists and has j|j+1 as one of its child
 // boundaries.  Its key range [f, l] is found by galloping + binary search
@@ -659,40 +707,9 @@ __global__ __launch_bounds__(256) void k_pairs(const uint64_t* __restrict__ ukey
   const uint64_t kj = key(j), kj1 = key(j + 1);
   const int s = split_level(kj, kj1);
   split[j] = s;
-  auto in_cell = [&](int m, uint64_t ref) { return (!ucid || ucid[m] == cj) && same_cell(key(m), ref, s); };
-  // first key of the cell: smallest f <= j with same_cell(ukey[f], kj, s)
-  int lo = j, step = 1;
-  while (true) {
-    int cand = j - step;
-    if (cand < 0 || !in_cell(cand, kj)) break;
-    lo = cand;
-    step <<= 1;
-  }
-  int hi_bad = j - step;  // < 0 or outside the cell
-  int a = hi_bad, b = lo;  // invariant: a outside (or -1), b inside
-  if (a < -1) a = -1;
-  while (b - a > 1) {
-    int m = a + (b - a) / 2;
-    if (in_cell(m, kj)) b = m; else a = m;
-  }
-  const int f = b;
-  // last key of the cell: largest l >= j+1 with same_cell(ukey[l], kj1, s)
-  int up = j + 1;
-  step = 1;
-  while (true) {
-    int cand = j + 1 + step;
-    if (cand >= U || !in_cell(cand, kj1)) break;
-    up = cand;
-    step <<= 1;
-  }
-  int c = up, d = j + 1 + step;  // c inside, d outside (or U)
-  if (d > U) d = U;
-  while (d - c > 1) {
-    int m = c + (d - c) / 2;
-    if (in_cell(m, kj1)) c = m; else d = m;
-  }
-  const int l = c;
-  bool is_rep = (f == j) || (s < kLevels - 1 && same_cell(key(f), kj, s + 1));
+  int f, l;
+  const bool is_rep = cell_range(
+      j, U, s, kj, kj1, key, [&](int m) { return !ucid || ucid[m] == cj; }, f, l);
   rep[j] = is_rep ? 1 : 0;
   pf[j] = f;
   pl[j] = l;
@@ -729,81 +746,42 @@ __global__ __launch_bounds__(256) void k_internal_write(const int32_t* __restric
 //   pre(internal v) = f + #internal nodes starting before f + #shallower nodes starting at f
 //   pre(leaf x)     = x + #internal nodes starting at or before x
 //   next(v)         = pre(leaf last(v)) + 1
-template <typename T4>
-__global__ __launch_bounds__(256) void k_nodes_internal(const Counts* __restrict__ cnt, const Cube* __restrict__ cubes,
-                                                        const int32_t* __restrict__ ucid,
-                                                        const int32_t* __restrict__ ilevel,
-                                                        const int32_t* __restrict__ ifirst,
-                                                        const int32_t* __restrict__ ilast,
-                                                        const int32_t* __restrict__ nstart,
-                                                        const int32_t* __restrict__ nexcl,
-                                                        const uint32_t* __restrict__ lmask,
-                                                        const int32_t* __restrict__ ustart,
-                                                        const uint64_t* __restrict__ ukey, Node* __restrict__ nodes,
-                                                        int32_t* __restrict__ nx, uint8_t* __restrict__ nlev,
-                                                        const int64_t* __restrict__ seg_off,
-                                                        const int32_t* __restrict__ croot,
-                                                        int32_t* __restrict__ anc, int nmax) {
-  int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= nmax || v >= cnt->n_internal) return;
-  const int s = ilevel[v], f = ifirst[v], l = ilast[v];
-  const int pre = f + nexcl[f] + __popc(lmask[f] & ((1u << s) - 1u));
-  const Cube* cube = cubes + (ucid ? ucid[f] : 0);
+__device__ __forceinline__ Node internal_node(const Cube& cube, uint64_t key, int s, int next, int first, int end) {
   Node nd;
-  nd.l = ldexp(cube->L, -s);
+  nd.l = ldexp(cube.L, -s);
   // the cube's centre, in the centre-of-mass fields until the moment passes
   // replace it (they need it for s, and for the centre of a massless cell)
-  const uint64_t prefix = (s == 0) ? 0ull : (ukey[f] >> (63 - 3 * s));
-  nd.cx = cube->lo[0] + ((double)compact3(prefix >> 2) + 0.5) * nd.l;
-  nd.cy = cube->lo[1] + ((double)compact3(prefix >> 1) + 0.5) * nd.l;
-  nd.cz = cube->lo[2] + ((double)compact3(prefix) + 0.5) * nd.l;
+  const uint64_t prefix = (s == 0) ? 0ull : (key >> (63 - 3 * s));
+  nd.cx = cube.lo[0] + ((double)compact3(prefix >> 2) + 0.5) * nd.l;
+  nd.cy = cube.lo[1] + ((double)compact3(prefix >> 1) + 0.5) * nd.l;
+  nd.cz = cube.lo[2] + ((double)compact3(prefix) + 0.5) * nd.l;
   nd.M = 0.0;
   nd.s = 0.0;
-  nd.next = l + nexcl[l] + nstart[l] + 1;
-  nd.first = ustart[f];
-  nd.count = ustart[l + 1] - ustart[f];
+  nd.next = next;
+  nd.first = first;
+  nd.count = end - first;
   nd.meta = s << 8;
-  nodes[pre] = nd;
-  nx[pre] = nd.next;
-  nlev[pre] = (uint8_t)s;
-  // the node is an ancestor of the first node of every run that starts inside
-  // its subtree (the walk's runs: walk_segments)
-  if (anc) {
-    const int cl = ucid ? ucid[f] : 0;
-    const int r0 = croot[cl], r1 = croot[cl + 1];
-    const int runs = walk_segments(cluster_size(seg_off, cl, nmax));
-    const int len = max(1, (r1 - r0 + runs - 1) / runs);
-    const int end = min(nd.next, r1) - r0;
-    for (int q = (pre - r0) / len + 1; q < runs && q * len < end; ++q)
-      anc[((int64_t)cl * kMaxRuns + q) * kAncSlots + s] = pre;
-  }
+  return nd;
 }
 
+// Internal node `pre` of level s is an ancestor of the first node of every run
+// (walk_segments) that starts inside its subtree.
+__device__ __forceinline__ void list_ancestor(int32_t* __restrict__ anc, int r0, int r1, int runs, int pre, int next,
+                                              int s) {
+  const int len = max(1, (r1 - r0 + runs - 1) / runs);
+  const int end = min(next, r1) - r0;
+  for (int q = (pre - r0) / len + 1; q < runs && q * len < end; ++q) anc[q * kAncSlots + s] = pre;
+}
+
+// The leaf of unique key number x at preorder id `pre`, its particles [first,
+// first + count) and its moments.  sl, sr: split levels towards the neighbouring
+// keys (-1: none, or another cluster's).
 template <typename T4>
-__global__ __launch_bounds__(256) void k_nodes_leaf(const Counts* __restrict__ cnt, const Cube* __restrict__ cubes,
-                                                    const int32_t* __restrict__ ucid,
-                                                    const int32_t* __restrict__ split,
-                                                    const int32_t* __restrict__ nstart,
-                                                    const int32_t* __restrict__ nexcl,
-                                                    const int32_t* __restrict__ ustart, const T4* __restrict__ ps,
-                                                    Node* __restrict__ nodes, Mom* __restrict__ mom,
-                                                    int32_t* __restrict__ nx, uint8_t* __restrict__ nlev, int nmax) {
-  int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int U = cnt->n_unique;
-  if (x >= nmax || x >= U) return;
-  const int pre = x + nexcl[x] + nstart[x];
-  const int first = ustart[x], count = ustart[x + 1] - first;
-  const Cube* cube = cubes + (ucid ? ucid[x] : 0);
+__device__ __forceinline__ Node leaf_node(const Cube* __restrict__ cube, int pre, int first, int count, int sl, int sr,
+                                          const T4* __restrict__ ps, Mom& mo) {
   // a leaf sits one level below the deeper of its two neighbour splits (split
   // -1 marks a cluster edge, so a cluster's only key is its level-0 root)
-  int level;
-  if (count > 1) {
-    level = kLevels;
-  } else {
-    int sl = (x > 0) ? split[x - 1] : -1;
-    int sr = (x < U - 1) ? split[x] : -1;
-    level = 1 + max(sl, sr);
-  }
+  const int level = count > 1 ? kLevels : 1 + max(sl, sr);
   Node nd;
   double M = 0.0, X = 0.0, Y = 0.0, Z = 0.0;
   for (int k = first; k < first + count; ++k) {
@@ -846,10 +824,59 @@ __global__ __launch_bounds__(256) void k_nodes_leaf(const Counts* __restrict__ c
   nd.first = first;
   nd.count = count;
   nd.meta = 1 | (count > 1 ? 2 : 0) | (level << 8);
+  mo = Mom{M, X, Y, Z};
+  return nd;
+}
+
+template <typename T4>
+__global__ __launch_bounds__(256) void k_nodes_internal(const Counts* __restrict__ cnt, const Cube* __restrict__ cubes,
+                                                        const int32_t* __restrict__ ucid,
+                                                        const int32_t* __restrict__ ilevel,
+                                                        const int32_t* __restrict__ ifirst,
+                                                        const int32_t* __restrict__ ilast,
+                                                        const int32_t* __restrict__ nstart,
+                                                        const int32_t* __restrict__ nexcl,
+                                                        const uint32_t* __restrict__ lmask,
+                                                        const int32_t* __restrict__ ustart,
+                                                        const uint64_t* __restrict__ ukey, Node* __restrict__ nodes,
+                                                        int32_t* __restrict__ nx, uint8_t* __restrict__ nlev,
+                                                        const int64_t* __restrict__ seg_off,
+                                                        const int32_t* __restrict__ croot,
+                                                        int32_t* __restrict__ anc, int nmax) {
+  int v = blockIdx.x * blockDim.x + threadIdx.x;
+  if (v >= nmax || v >= cnt->n_internal) return;
+  const int s = ilevel[v], f = ifirst[v], l = ilast[v];
+  const int pre = f + nexcl[f] + __popc(lmask[f] & ((1u << s) - 1u));
+  const int cl = ucid ? ucid[f] : 0;
+  const Node nd = internal_node(cubes[cl], ukey[f], s, l + nexcl[l] + nstart[l] + 1, ustart[f], ustart[l + 1]);
   nodes[pre] = nd;
-  mom[pre] = Mom{M, X, Y, Z};
+  nx[pre] = nd.next;
+  nlev[pre] = (uint8_t)s;
+  if (anc)
+    list_ancestor(anc + (int64_t)cl * kMaxRuns * kAncSlots, croot[cl], croot[cl + 1],
+                  walk_segments(cluster_size(seg_off, cl, nmax)), pre, nd.next, s);
+}
+
+template <typename T4>
+__global__ __launch_bounds__(256) void k_nodes_leaf(const Counts* __restrict__ cnt, const Cube* __restrict__ cubes,
+                                                    const int32_t* __restrict__ ucid,
+                                                    const int32_t* __restrict__ split,
+                                                    const int32_t* __restrict__ nstart,
+                                                    const int32_t* __restrict__ nexcl,
+                                                    const int32_t* __restrict__ ustart, const T4* __restrict__ ps,
+                                                    Node* __restrict__ nodes, Mom* __restrict__ mom,
+                                                    int32_t* __restrict__ nx, uint8_t* __restrict__ nlev, int nmax) {
+  int x = blockIdx.x * blockDim.x + threadIdx.x;
+  const int U = cnt->n_unique;
+  if (x >= nmax || x >= U) return;
+  const int pre = x + nexcl[x] + nstart[x];
+  Mom mo;
+  const Node nd = leaf_node(cubes + (ucid ? ucid[x] : 0), pre, ustart[x], ustart[x + 1] - ustart[x],
+                            x > 0 ? split[x - 1] : -1, x < U - 1 ? split[x] : -1, ps, mo);
+  nodes[pre] = nd;
+  mom[pre] = mo;
   nx[pre] = pre + 1;
-  nlev[pre] = (uint8_t)level;
+  nlev[pre] = (uint8_t)(nd.meta >> 8);
 }
 
 // ---------------------------------------------------------------- moments
@@ -1233,24 +1260,27 @@ static int hilbert_levels(int K) {
 // particle's cell `levels` below the cluster's root cube (the grid coordinates
 // are those of the Morton keys).
 template <typename T4>
+__device__ __forceinline__ uint32_t hilbert_key(const Cube& cube, const T4& p, int levels) {
+  const double c[3] = {(double)p.x, (double)p.y, (double)p.z};
+  uint32_t q[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    double t = floor((c[d] - cube.lo[d]) * cube.scale);
+    if (!(t >= 0.0)) t = 0.0;
+    if (t > (double)(kGrid - 1)) t = (double)(kGrid - 1);
+    q[d] = (uint32_t)t >> (kLevels - levels);
+  }
+  return hilbert3(q[0], q[1], q[2], levels);
+}
+
+template <typename T4>
 __global__ __launch_bounds__(256) void k_hkeys(const T4* __restrict__ ps, int n, const Cube* __restrict__ cubes,
                                                const int32_t* __restrict__ scid, int levels,
                                                uint64_t* __restrict__ keys, int32_t* __restrict__ idx) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= n) return;
   const int cl = scid ? scid[k] : 0;
-  const Cube* cube = cubes + cl;
-  const T4 p = ps[k];
-  const double c[3] = {(double)p.x, (double)p.y, (double)p.z};
-  uint32_t q[3];
-#pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    double t = floor((c[d] - cube->lo[d]) * cube->scale);
-    if (!(t >= 0.0)) t = 0.0;
-    if (t > (double)(kGrid - 1)) t = (double)(kGrid - 1);
-    q[d] = (uint32_t)t >> (kLevels - levels);
-  }
-  keys[k] = ((uint64_t)(uint32_t)cl << (3 * levels)) | hilbert3(q[0], q[1], q[2], levels);
+  keys[k] = ((uint64_t)(uint32_t)cl << (3 * levels)) | hilbert_key(cubes[cl], ps[k], levels);
   idx[k] = k;
 }
 
@@ -1276,6 +1306,368 @@ static hipError_t hilbert_impl(int n, const BuildWs& w, hipStream_t st) {
   }
   if (vin != w.horder) k_copy_kv<<<nblk(n, 256), 256, 0, st>>>(kin, vin, kout, w.horder, n);
   return hipGetLastError();
+}
+
+// ---------------------------------------------------------------- small trees
+// The whole build of a single tree of at most kSmallBuild particles by one
+// workgroup: the same steps as the kernels above with the keys, the topology
+// and the level lists in LDS (keys, indices, node links and lists fill 152 KB
+// of it), a barrier where they have a launch.  It ends with the Hilbert walk
+// order.  As a sequence of kernels a small build is bound by its launches, some
+// 95 of about 4 us (340 us for 1000 particles, 390 us for 4096 in FP64); here it
+// is bound by the latency of one workgroup's steps: 82 and 142 us.  More
+// particles do not fit the LDS.
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallWaves = kSmallThreads / kWave;
+constexpr int kSmallItems = kSmallBuild / kSmallThreads;
+
+struct SmallLds {
+  union {
+    struct {
+      uint64_t key[2][kSmallBuild];
+      int32_t idx[2][kSmallBuild];
+      uint32_t hist[kSmallWaves][256];
+    } sort;
+    struct {
+      int32_t nx[2 * kSmallBuild];     // (over key[0], which holds the sorted keys until ukey is written)
+      uint64_t ukey[kSmallBuild];      // (over key[1])
+      int32_t nstart[kSmallBuild + 4]; // (from here over idx and hist, free once the particles are gathered)
+      int32_t nexcl[kSmallBuild + 4];
+      uint32_t lmask[kSmallBuild];
+    } topo;
+  };
+  int32_t ustart[kSmallBuild + 4];
+  uint16_t ord[kSmallBuild];           // internal nodes by level
+  int8_t split[kSmallBuild];
+  uint8_t lv[2 * kSmallBuild];
+  int32_t start[kLevels + 2], fill[kLevels + 1];
+  int32_t scan[kSmallWaves];
+  double red[6][kSmallWaves];
+  Cube cube;
+  int32_t bad;
+};
+static_assert(sizeof(SmallLds) <= 160 * 1024, "the small build's arrays must fit the LDS");
+
+// One stable pass by the 8-bit digit at `shift`, buffer b to buffer b ^ 1: each
+// wave ranks its contiguous share in input order (as k_rs_scatter does), then
+// the counts are scanned digit by digit, wave by wave.
+__device__ __forceinline__ void small_sort_pass(SmallLds& s, int n, int shift, int b) {
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  for (int k = t; k < kSmallWaves * 256; k += kSmallThreads) s.sort.hist[0][k] = 0;
+  __syncthreads();
+  constexpr int kRounds = kSmallBuild / kSmallThreads;
+  const int rounds = (n + kSmallThreads - 1) / kSmallThreads;  // 64 items of each wave
+  uint64_t key[kRounds];
+  int32_t val[kRounds];
+  uint32_t rank[kRounds];
+  const uint64_t lt = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    if (r >= rounds) break;
+    const int j = (w * rounds + r) * kWave + lane;
+    const bool valid = j < n;
+    key[r] = valid ? s.sort.key[b][j] : 0ull;
+    val[r] = valid ? s.sort.idx[b][j] : 0;
+    const uint32_t d = (uint32_t)(key[r] >> shift) & 255u;
+    uint64_t peers = ballot(valid);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const bool bit = (d >> q) & 1u;
+      const uint64_t mk = ballot(bit);
+      peers &= bit ? mk : ~mk;
+    }
+    const int leader = valid ? __builtin_ctzll(peers) : lane;
+    uint32_t base = 0;
+    if (valid && lane == leader) base = atomicAdd(&s.sort.hist[w][d], (uint32_t)__popcll(peers));
+    rank[r] = __shfl(base, leader, 64) + (uint32_t)__popcll(peers & lt);
+  }
+  __syncthreads();
+  uint32_t h[kSmallWaves], c = 0;
+  if (t < 256)
+#pragma unroll
+    for (int k = 0; k < kSmallWaves; ++k) c += h[k] = s.sort.hist[k][t];
+  int tot;
+  uint32_t run = (uint32_t)block_excl_scan<kSmallThreads>((int)c, s.scan, &tot);
+  if (t < 256)
+#pragma unroll
+    for (int k = 0; k < kSmallWaves; ++k) {
+      s.sort.hist[k][t] = run;
+      run += h[k];
+    }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    const int j = (w * rounds + r) * kWave + lane;
+    if (r < rounds && j < n) {
+      const uint32_t q = s.sort.hist[w][(uint32_t)(key[r] >> shift) & 255u] + rank[r];
+      s.sort.key[b ^ 1][q] = key[r];
+      s.sort.idx[b ^ 1][q] = val[r];
+    }
+  }
+  __syncthreads();
+}
+
+struct SmallArgs {
+  int n;
+  Cube* cube;
+  Counts* counts;
+  const int64_t* seg_off;  // the caller's offsets {0, n}, to be checked (null: none)
+  int64_t* own_off;        // the tree's own, to be written
+  int32_t* croot;
+  int32_t* perm;
+  void* ps;
+  Node* nodes;
+  Mom* mom;
+  int32_t* nx;
+  uint8_t* nlev;
+  int32_t *obkt, *okids;
+  int32_t* anc;
+  int32_t* horder;
+  int nchunks, hlevels;
+};
+
+template <typename T, typename T4>
+__global__ __launch_bounds__(kSmallThreads) void k_build_small(const T* __restrict__ pos, const T* __restrict__ mass,
+                                                               SmallArgs a) {
+  __shared__ SmallLds s;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, n = a.n;
+  T4* ps = reinterpret_cast<T4*>(a.ps);
+
+  // root cube
+  {
+    double v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    bool bad = false;
+    for (int i = t; i < n; i += kSmallThreads) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const double x = (double)pos[3 * i + d];
+        if (!isfinite(x)) {
+          bad = true;
+        } else {
+          v[d] = fmin(v[d], x);
+          v[3 + d] = fmax(v[3 + d], x);
+        }
+      }
+      if (!isfinite((double)mass[i])) bad = true;
+    }
+    if (t == 0) s.bad = 0;
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+      for (int o = 32; o > 0; o >>= 1) {
+        const double u = __shfl_xor(v[q], o, 64);
+        v[q] = q < 3 ? fmin(v[q], u) : fmax(v[q], u);
+      }
+      if (lane == 0) s.red[q][w] = v[q];
+    }
+    for (int k = t; k < kMaxRuns * kAncSlots; k += kSmallThreads) a.anc[k] = -1;
+    for (int k = t; k < kLevels * a.nchunks; k += kSmallThreads) a.obkt[k] = -1;
+    __syncthreads();
+    if (bad) atomicOr(&s.bad, 1);
+    if (t == 0) {
+      double lo[3], hi[3];
+      for (int d = 0; d < 3; ++d) {
+        lo[d] = s.red[d][0];
+        hi[d] = s.red[3 + d][0];
+        for (int k = 1; k < kSmallWaves; ++k) {
+          lo[d] = fmin(lo[d], s.red[d][k]);
+          hi[d] = fmax(hi[d], s.red[3 + d][k]);
+        }
+      }
+      finish_cube(lo, hi, &s.cube);
+      if (a.seg_off) {
+        if (a.seg_off[0] != 0 || a.seg_off[1] != n) atomicOr(&s.bad, 2);
+      } else {
+        a.own_off[0] = 0;
+        a.own_off[1] = n;
+      }
+    }
+    __syncthreads();
+  }
+  const Cube cube = s.cube;
+
+  // keys, stable sort, gather
+  for (int i = t; i < n; i += kSmallThreads) {
+    s.sort.key[0][i] = morton_key(cube, pos, i);
+    s.sort.idx[0][i] = i;
+  }
+  __syncthreads();
+  for (int pass = 0; pass < 8; ++pass) small_sort_pass(s, n, 8 * pass, pass & 1);
+  for (int k = t; k < n; k += kSmallThreads) {
+    const int j = s.sort.idx[0][k];
+    a.perm[k] = j;
+    T4 v;
+    v.x = pos[3 * j];
+    v.y = pos[3 * j + 1];
+    v.z = pos[3 * j + 2];
+    v.w = mass[j];
+    ps[k] = v;
+  }
+
+  // unique keys, kSmallItems consecutive positions per thread
+  int U;
+  {
+    uint64_t key[kSmallItems];
+    bool fl[kSmallItems];
+    int c = 0;
+#pragma unroll
+    for (int k = 0; k < kSmallItems; ++k) {
+      const int j = t * kSmallItems + k;
+      key[k] = j < n ? s.sort.key[0][j] : 0ull;
+      fl[k] = j < n && (j == 0 || key[k] != s.sort.key[0][j - 1]);
+      c += fl[k] ? 1 : 0;
+    }
+    int u = block_excl_scan<kSmallThreads>(c, s.scan, &U);  // (its barriers end the reads of idx and hist)
+#pragma unroll
+    for (int k = 0; k < kSmallItems; ++k)
+      if (fl[k]) {
+        s.topo.ukey[u] = key[k];
+        s.ustart[u] = t * kSmallItems + k;
+        ++u;
+      }
+    if (t == 0) s.ustart[U] = n;
+    for (int k = t; k <= U; k += kSmallThreads) s.topo.nstart[k] = 0;
+    for (int k = t; k < U; k += kSmallThreads) s.topo.lmask[k] = 0;
+    if (t <= kLevels) s.fill[t] = 0;
+  }
+  __syncthreads();
+
+  // internal nodes: the pairs that are their cell's first child boundary
+  int nf[kSmallItems], nl[kSmallItems], ns[kSmallItems];  // first and last key, level (-1: none)
+#pragma unroll
+  for (int k = 0; k < kSmallItems; ++k) {
+    const int j = t + k * kSmallThreads;
+    ns[k] = -1;
+    nf[k] = nl[k] = 0;
+    if (j >= U - 1) continue;
+    const uint64_t kj = s.topo.ukey[j], kj1 = s.topo.ukey[j + 1];
+    const int lev = split_level(kj, kj1);
+    s.split[j] = (int8_t)lev;
+    if (cell_range(
+            j, U, lev, kj, kj1, [&](int m) { return s.topo.ukey[m]; }, [](int) { return true; }, nf[k], nl[k])) {
+      ns[k] = lev;
+      atomicAdd(&s.topo.nstart[nf[k]], 1);
+      atomicOr(&s.topo.lmask[nf[k]], 1u << lev);
+      atomicAdd(&s.fill[lev], 1);
+    }
+  }
+  __syncthreads();
+  int I;
+  {
+    int v[kSmallItems], c = 0;
+#pragma unroll
+    for (int k = 0; k < kSmallItems; ++k) {
+      const int x = t * kSmallItems + k;
+      v[k] = x < U ? s.topo.nstart[x] : 0;
+      c += v[k];
+    }
+    int e = block_excl_scan<kSmallThreads>(c, s.scan, &I);
+#pragma unroll
+    for (int k = 0; k < kSmallItems; ++k) {
+      const int x = t * kSmallItems + k;
+      if (x < U) s.topo.nexcl[x] = e;
+      e += v[k];
+    }
+    if (t == 0) {
+      int run = 0;
+      for (int L = 0; L <= kLevels; ++L) {
+        s.start[L] = run;
+        run += s.fill[L];
+        s.fill[L] = 0;
+      }
+      s.start[kLevels + 1] = run;
+      a.croot[0] = 0;
+      a.croot[1] = U + I;
+      *a.cube = cube;
+      Counts cn{};
+      cn.n_unique = U;
+      cn.n_internal = I;
+      cn.n_nodes = U + I;
+      cn.bad_input = s.bad;
+      *a.counts = cn;
+    }
+  }
+  __syncthreads();
+
+  // node records (the sorted keys in key[0] are no longer needed: nx takes their place)
+  const int m = U + I;
+#pragma unroll
+  for (int k = 0; k < kSmallItems; ++k) {
+    if (ns[k] < 0) continue;
+    const int f = nf[k], l = nl[k], lev = ns[k];
+    const int pre = f + s.topo.nexcl[f] + __popc(s.topo.lmask[f] & ((1u << lev) - 1u));
+    const Node nd = internal_node(cube, s.topo.ukey[f], lev, l + s.topo.nexcl[l] + s.topo.nstart[l] + 1, s.ustart[f],
+                                  s.ustart[l + 1]);
+    a.nodes[pre] = nd;
+    a.nx[pre] = s.topo.nx[pre] = nd.next;
+    a.nlev[pre] = s.lv[pre] = (uint8_t)lev;
+    s.ord[s.start[lev] + atomicAdd(&s.fill[lev], 1)] = (uint16_t)pre;
+    list_ancestor(a.anc, 0, m, walk_segments(n), pre, nd.next, lev);
+    // (one node of a level straddles a chunk's end at most: the second moments' lists)
+    const int ch = pre / kChunk;
+    if (nd.next > (ch + 1) * kChunk) a.obkt[min(lev, kLevels - 1) * a.nchunks + ch] = pre;
+  }
+  for (int x = t; x < U; x += kSmallThreads) {
+    const int pre = x + s.topo.nexcl[x] + s.topo.nstart[x];
+    Mom mo;
+    const Node nd = leaf_node(&s.cube, pre, s.ustart[x], s.ustart[x + 1] - s.ustart[x], x > 0 ? s.split[x - 1] : -1,
+                              x < U - 1 ? s.split[x] : -1, ps, mo);
+    a.nodes[pre] = nd;
+    a.mom[pre] = mo;
+    a.nx[pre] = s.topo.nx[pre] = pre + 1;
+    a.nlev[pre] = s.lv[pre] = (uint8_t)(nd.meta >> 8);
+  }
+  __syncthreads();
+
+  // moments, deepest level first, and the straddling nodes' children
+  for (int L = kLevels; L >= 0; --L) {
+    const int b = s.start[L], e = s.start[L + 1];
+    if (b == e) continue;
+    for (int j = b + t; j < e; j += kSmallThreads) {
+      const int p = s.ord[j], end = s.topo.nx[p];
+      Mom q{0.0, 0.0, 0.0, 0.0};
+      int c = p + 1;
+      for (int k = 0; k < 8 && c < end; ++k, c = max(s.topo.nx[c], c + 1)) add_mom(q, a.mom[c]);
+      const double ctr[3] = {a.nodes[p].cx, a.nodes[p].cy, a.nodes[p].cz};
+      finish_node(p, q, ctr, a.nodes, a.mom);
+    }
+    __syncthreads();
+  }
+  for (int slot = t; slot < kLevels * a.nchunks; slot += kSmallThreads) {
+    const int p = a.obkt[slot];
+    if (p < 0) continue;
+    const int end = s.topo.nx[p];
+    int k = 0;
+    for (int c = p + 1; k < 8 && c < end; ++k, c = max(s.topo.nx[c], c + 1)) a.okids[8 * slot + k] = c;
+    for (; k < 8; ++k) a.okids[8 * slot + k] = -1;
+  }
+  __syncthreads();
+
+  // Hilbert walk order
+  for (int k = t; k < n; k += kSmallThreads) {
+    s.sort.key[0][k] = hilbert_key(cube, ps[k], a.hlevels);
+    s.sort.idx[0][k] = k;
+  }
+  __syncthreads();
+  int b = 0;
+  for (int shift = 0; shift < 3 * a.hlevels; shift += 8, b ^= 1) small_sort_pass(s, n, shift, b);
+  for (int k = t; k < n; k += kSmallThreads) a.horder[k] = s.sort.idx[b][k];
+}
+
+template <typename T, typename T4>
+static hipError_t build_small_impl(const T* pos, const T* mass, int n, const BuildWs& w, hipStream_t st) {
+  if (n < 1 || n > kSmallBuild || w.n_seg != 1 || !w.anc) return hipErrorInvalidValue;
+  SmallArgs a{n,      w.cube, w.counts, w.seg_off == w.own_off ? nullptr : w.seg_off, w.own_off, w.croot, w.idx_a, w.ps,
+              w.nodes, w.mom,  w.nx,     w.nlev, w.obkt, w.okids, w.anc, w.horder, (int)n_chunks(n), hilbert_levels(1)};
+  k_build_small<T, T4><<<1, kSmallThreads, 0, st>>>(pos, mass, a);
+  return hipGetLastError();
+}
+
+hipError_t build_small_f32(const float* pos, const float* mass, int n, const BuildWs& w, hipStream_t st) {
+  return build_small_impl<float, float4>(pos, mass, n, w, st);
+}
+
+hipError_t build_small_f64(const double* pos, const double* mass, int n, const BuildWs& w, hipStream_t st) {
+  return build_small_impl<double, double4>(pos, mass, n, w, st);
 }
 
 // The walk order of the targets as caller indices: out[k] = perm[order[k]]

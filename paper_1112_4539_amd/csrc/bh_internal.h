@@ -111,6 +111,11 @@ hipError_t build_tree_f32(const float* pos, const float* mass, int n, const Buil
                           hipStream_t st);
 hipError_t build_tree_f64(const double* pos, const double* mass, int n, const BuildWs& w, const BuildFork* fork,
                           hipStream_t st);
+// The build of a single tree of 1 to kSmallBuild particles, with the Hilbert
+// order, in one launch.
+constexpr int kSmallBuild = 4096;
+hipError_t build_small_f32(const float* pos, const float* mass, int n, const BuildWs& w, hipStream_t st);
+hipError_t build_small_f64(const double* pos, const double* mass, int n, const BuildWs& w, hipStream_t st);
 hipError_t fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st);
 // Walk order of the targets (w.horder): Morton positions sorted by cluster and
 // the Hilbert index of their cell a few levels below the cluster's root cube.

@@ -263,18 +263,20 @@ hipError_t ensure_target_order(const bh_tree* t, hipStream_t st) {
   return hipSuccess;
 }
 
-// Waves that share a group's walk (1: one wave per group).  Measured, build and
-// walk: Plummer 1000 FP32 594 us with one wave and 408 with 16; 4096 FP64 770 and
-// 434; clumpy 30,000 825, 644 with 8 and 752 with 16; Plummer 60,000 at theta 0.35
-// 1639 and 1028 with 4; 100,003 1182 and 1036 with 4.  Beyond that the groups fill
-// the chip by themselves, and waves waiting for the last run of their group cost
-// more than they bring (clumpy 130,000: 1050, 1163 with 4).  In a forest, where
-// the clusters have more runs than one tree of that size, 8 is the better choice
-// (20 clusters, 56,000 particles: 1031, 755 with 4, 681 with 8).
-int split_waves(int64_t n, int64_t n_seg) {
+// Waves that share a group's walk (1: one wave per group).  Walk times with 1, 4,
+// 8 and 16 waves, us: Plummer 1000 FP32 211, 74, 46, 32; 4096 FP64 398, 143, 93,
+// 69; clumpy 10,000 250, 99, 92, 91; 30,000 349, 187, 186, 183; 60,000 of order 2
+// 839, 398, 560, 1021; Plummer 100,003 703, 423, 563, 836.  Beyond that the groups
+// fill the chip by themselves, and waves waiting for the last run of their group
+// cost more than they bring (clumpy 200,003: 659, 973 with 4).  A forest's clusters
+// may have the most runs, whose sums leave a CU LDS for two workgroups: 16 waves
+// (20 clusters, 56,000 particles: 508, 285, 182, 139).  The registers of walks of
+// order 2 hold one workgroup of 16 waves per CU.
+int split_waves(int64_t n, int64_t n_seg, int order) {
   const int64_t groups = (n + 63) / 64;
   if (n > bh::kSplitMaxN) return 1;
-  return groups <= 256 ? 16 : groups <= 512 || n_seg > 1 ? 8 : 4;
+  if (groups <= 256 || n_seg > 1) return 16;
+  return groups <= 512 ? (order == 2 ? 8 : 16) : 4;
 }
 
 int run_walk(const bh_tree* t, double theta, const float* theta_group, double eps, void* acc, void* pot,
@@ -357,7 +359,7 @@ int run_walk(const bh_tree* t, double theta, const float* theta_group, double ep
   // groups alone would leave SIMDs without waves.
   if (mode == bh::kWalkForces && a.anc && !a.persistent && a.waves_per_block == 1 && a.lds_share64 == 0 &&
       a.targets_per_lane == 1) {
-    a.split_waves = split_waves(t->n, t->n_seg);
+    a.split_waves = split_waves(t->n, t->n_seg, t->order);
   }
   if (a.persistent) {
     a.grid = bh::persistent_grid(t->prec == BH_FP64, t->order == 2 ? (mode | bh::kWalkQuad) : mode, eps * eps > 0.0,

@@ -38,14 +38,17 @@ inline int64_t n_chunks(int64_t n) { return (2 * (n > 0 ? n : 1) + kChunk - 1) /
 // Runs of a cluster's subtree: a walk sums a target's terms run by run (equally
 // many preorder nodes each) and adds the runs' sums in order.  Several waves can
 // then share a group's walk; the cuts depend on the cluster's size alone, so
-// that a cluster's results do not depend on how it is walked.  Small clusters,
-// whose few groups leave the chip idle, get more runs.
-constexpr int kMaxRuns = 24;
+// that a cluster's results do not depend on how it is walked.  More runs balance
+// the waves better (the run next to a group's targets holds the most work); what
+// limits them is that the workgroups a CU needs at once keep their runs' sums, 2
+// KB each, in its LDS: two workgroups up to 32,768 particles, four up to 65,536,
+// seven up to 102,400.
+constexpr int kMaxRuns = 36;           // (two workgroups of 36 runs fill the 160 KB of a CU)
 constexpr int kAncSlots = 24;          // ancestors of a run's first node, by level (kLevels of them used)
 constexpr int kAncClusters = 1024;     // forests of at most this many clusters keep the lists
 constexpr int kMaxSplitWaves = 16;     // waves that share a group
 constexpr int64_t kSplitMaxN = 102400; // largest tree whose groups are shared (1600 groups)
-__host__ __device__ inline int walk_segments(int64_t n) { return n <= 32768 ? 24 : n <= kSplitMaxN ? 16 : 1; }
+__host__ __device__ inline int walk_segments(int64_t n) { return n <= 32768 ? 36 : n <= 65536 ? 18 : n <= kSplitMaxN ? 10 : 1; }
 // Particles of cluster k (the offsets clamped to [0, n]).
 __host__ __device__ inline int64_t cluster_size(const int64_t* off, int k, int64_t n) {
   const int64_t b = off[k] < 0 ? 0 : off[k] > n ? n : off[k];

@@ -872,7 +872,15 @@ __device__ __forceinline__ void split_cluster(const WalkArgs& a, StepNode<kF64, 
   const int lane = __lane_id();
   Target<kF64>& T = C.t[0];
   const int len = run_length(r0, r1, runs);
-  for (int s = w; s < runs;) {
+  // Runs are taken outwards from the one the group's targets lie in (leaves are
+  // spread over the runs as the particles are): it and its neighbours hold most
+  // of the work, and the longest pieces go first.
+  const uint64_t m_mine = ballot(mine);
+  const int at = m_mine ? __builtin_amdgcn_readlane(T.i, __builtin_ctzll(m_mine)) : 0;
+  const int64_t first = a.seg_off[k], size = max((int64_t)1, cluster_size(a.seg_off, k, a.n));
+  const int home = uniform((int)min(max((at - first) * runs / size, (int64_t)0), (int64_t)runs - 1));
+  for (int turn = w; turn < runs;) {
+    const int s = (home + ((turn & 1) ? (turn + 1) >> 1 : runs - (turn >> 1))) % runs;
     const int c0 = r0 + s * len, end = min(c0 + len, r1);
     if (c0 < end) {
       T.skip = mine ? r0 : 0x7fffffff;
@@ -895,13 +903,17 @@ __device__ __forceinline__ void split_cluster(const WalkArgs& a, StepNode<kF64, 
     T.acc.init();
     int nx = 0;
     if (lane == 0) nx = atomicAdd(ticket, 1);
-    s = uniform(nx);
+    turn = uniform(nx);
   }
 }
 
-// One workgroup per group of 64 targets (forces; one target per lane).
+// One workgroup per group of 64 targets (forces; one target per lane).  (Monopole
+// kernels are asked for 8 waves per SIMD, so that two workgroups of 16 fit a CU:
+// clumpy 30,000 took 328 us with one, 209 with two, at 16 runs.)
 template <bool kF64, int kMode, bool kSoft, bool kGroupTheta>
-__global__ __launch_bounds__(kWave * kMaxSplitWaves) void k_walk_split(WalkArgs a) {
+__global__ __launch_bounds__(kWave * kMaxSplitWaves)
+__attribute__((amdgpu_waves_per_eu(kMode == kWalkForces ? 8 : 4)))
+void k_walk_split(WalkArgs a) {
   using R = typename std::conditional<kF64, double, float>::type;
   extern __shared__ double dyn_lds[];
   double (*part)[4][kWave] = reinterpret_cast<double (*)[4][kWave]>(dyn_lds);

@@ -31,7 +31,7 @@ def _same(T, **kw):
 
 
 @pytest.mark.parametrize("prec", [torch.float32, torch.float64])
-@pytest.mark.parametrize("n", [1, 2, 3, 9, 63, 64, 65, 500, 1000, 16384, 16385, 32768, 32769, 102400, 102401])
+@pytest.mark.parametrize("n", [1, 2, 3, 9, 63, 64, 65, 500, 1000, 16384, 16385, 32768, 32769, 65536, 65537, 102400, 102401])
 def test_split_sizes(bh, n, prec):
     print(f"[split] n={n} {prec}", flush=True)
     pos, mass = inputs.plummer(n, n)

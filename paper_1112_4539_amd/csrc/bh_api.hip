@@ -125,6 +125,7 @@ size_t layout(int64_t n, int64_t K, int prec, char* base, bh::BuildWs* w, int32_
   t.nlev = reinterpret_cast<uint8_t*>(take(nodes));
   t.obkt = reinterpret_cast<int32_t*>(take(4 * bh::kLevels * (size_t)bh::n_chunks((int64_t)N)));
   t.okids = reinterpret_cast<int32_t*>(take(32 * bh::kLevels * (size_t)bh::n_chunks((int64_t)N)));
+  t.sbkt = reinterpret_cast<int32_t*>(take(4 * bh::kLevels * (size_t)bh::n_super((int64_t)N)));
   t.anc = K <= bh::kAncClusters
               ? reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)K * bh::kMaxRuns * bh::kAncSlots))
               : nullptr;

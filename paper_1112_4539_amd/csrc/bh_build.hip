@@ -882,15 +882,13 @@ __global__ __launch_bounds__(256) void k_nodes_leaf(const Counts* __restrict__ c
 // ---------------------------------------------------------------- moments
 // The moments of an internal node fold its children's, in octant order (the
 // preorder of the children p+1, next(p+1), ... < next(p)).  The fold runs
-// bottom-up in two launches, with the same arithmetic for every node:
+// bottom-up, with the same arithmetic for every node:
 //  * k_moments_chunk: a workgroup loads a chunk of kChunk consecutive preorder
 //    nodes (next, level, the leaves' moments) into LDS and folds there, level
 //    by level (deepest first), every internal node whose subtree ends inside
 //    the chunk.  The others, at most one per level, go to the chunk's slot of
-//    their level's list, and k_open_kids lists their children (along next,
-//    which past the chunk's end continues in memory);
-//  * k_moments_top: one launch per level folds that level's listed nodes
-//    from their children's records in memory.
+//    their level's list;
+//  * k_moments_super and k_moments_final fold the listed nodes.
 // A node's children are deeper than it, so each fold reads finished values.
 
 // Per-chunk index in LDS: next of every node, and the internal nodes whose
@@ -1039,46 +1037,143 @@ __global__ __launch_bounds__(kChunkThreads) void k_moments_chunk(const Counts* _
   }
 }
 
-// Children of the listed straddling nodes, along next (past the chunk's end
-// the chain continues in memory), -1 after the last.
-__global__ __launch_bounds__(256) void k_open_kids(const Counts* __restrict__ cnt, const int32_t* __restrict__ obkt,
-                                                   const int32_t* __restrict__ nx, int nchunks,
-                                                   int32_t* __restrict__ okids) {
-  const int64_t slot = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (slot >= (int64_t)kLevels * nchunks) return;
-  const int L = (int)(slot / nchunks), j = (int)(slot - (int64_t)L * nchunks);
-  const int n_nodes = cnt->n_nodes;
-  if ((int64_t)j * kChunk >= n_nodes) return;  // a chunk past the last node
-  const int p = obkt[slot];
-  if (p < 0) return;
-  int k = 0;
-  if (p < n_nodes) {
-    const int end = min(nx[p], n_nodes);
-    for (int c = p + 1; k < 8 && c < end; ++k, c = max(nx[c], c + 1)) okids[8 * slot + k] = c;
-  }
-  for (; k < 8; ++k) okids[8 * slot + k] = -1;
+// The straddling nodes, in two launches.  k_moments_super: a workgroup takes
+// kSuper consecutive chunks, one thread per (level, chunk) slot; it lists its
+// node's children (along next, which past the chunk's end continues in memory;
+// the second moments read the list too), and the nodes whose subtree ends
+// inside the workgroup's chunks are folded level by level, deepest first, a
+// barrier apart.  What still straddles, at most one node per level and
+// workgroup, is listed for k_moments_final, one workgroup that does the same
+// over all of them.  (One launch per level, 21 of some 5 us, and one for the
+// lists took 79 us for 100,000 particles, 122 for 1M and 157 for 4M; the two take
+// 39, 50 and 159.)
+constexpr int kSuper = kSuperChunks;
+constexpr int kSuperSlots = kSuper * kLevels;
+constexpr int kSuperThreads = (kSuperSlots + kWave - 1) / kWave * kWave;
+constexpr int kFinalThreads = 1024;
+
+// Levels that some thread asks for (level < 0: none), as a mask (LDS word `m`).
+__device__ __forceinline__ uint32_t level_mask(uint32_t* m, int level) {
+  if (threadIdx.x == 0) *m = 0;
+  __syncthreads();
+  if (level >= 0) atomicOr(m, 1u << level);
+  __syncthreads();
+  return *m;
 }
 
-__global__ __launch_bounds__(256) void k_moments_top(const Counts* __restrict__ cnt, const int32_t* __restrict__ obkt,
-                                                     const int32_t* __restrict__ okids, int nchunks,
-                                                     Node* __restrict__ nodes, Mom* __restrict__ mom, int L) {
+// The slots of one workgroup of the super launches: calls fold(p, kids) for
+// every node that ends inside the workgroup's chunks, deepest level first.
+// load(slot, p, kids): the children of the slot's node; open(L, slot): a node
+// that is left over.
+template <typename Load, typename Open, typename Fold>
+__device__ __forceinline__ void fold_super(const Counts* __restrict__ cnt, const int32_t* __restrict__ obkt,
+                                           const int32_t* __restrict__ nx, int nchunks, Load&& load, Open&& open,
+                                           Fold&& fold) {
+  __shared__ uint32_t mask;
   const int n_nodes = cnt->n_nodes;
-  {
-    const int m = min((n_nodes + kChunk - 1) / kChunk, nchunks);
-    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < m; j += gridDim.x * blockDim.x) {
-      const int slot = L * nchunks + j;
-      const int p = obkt[slot];
-      if (p < 0 || p >= n_nodes) continue;
-      Mom q{0.0, 0.0, 0.0, 0.0};
-      for (int k = 0; k < 8; ++k) {
-        const int c = okids[8 * slot + k];
-        if (c <= p || c >= n_nodes) break;
-        add_mom(q, mom[c]);
+  const int L = threadIdx.x / kSuper, j = blockIdx.x * kSuper + threadIdx.x % kSuper;
+  if ((int64_t)blockIdx.x * kSuper * kChunk >= n_nodes) return;  // (the whole workgroup)
+  const int64_t end = min((int64_t)(blockIdx.x + 1) * kSuper * kChunk, (int64_t)n_nodes);
+  int p = -1, kids[8];
+  if (L < kLevels && j < nchunks && (int64_t)j * kChunk < n_nodes) {
+    const int slot = L * nchunks + j;
+    p = obkt[slot];
+    if (p >= n_nodes) p = -1;
+    if (p >= 0) {
+      load(slot, p, kids);
+      if (nx[p] > end) {
+        open(L, slot);
+        p = -1;
       }
-      const double ctr[3] = {nodes[p].cx, nodes[p].cy, nodes[p].cz};
-      finish_node(p, q, ctr, nodes, mom);
     }
   }
+  for (uint32_t left = level_mask(&mask, p >= 0 ? L : -1); left;) {
+    const int lv = 31 - __clz((int)left);
+    left &= ~(1u << lv);
+    if (p >= 0 && L == lv) fold(p, kids);
+    __syncthreads();
+  }
+}
+
+// The slots left over (sbkt [kLevels][nsuper]; -1: none), by one workgroup; the
+// lists of the next level's nodes are read before the barrier of the current
+// one.
+template <typename Fold>
+__device__ __forceinline__ void fold_final(const Counts* __restrict__ cnt, const int32_t* __restrict__ obkt,
+                                           const int32_t* __restrict__ okids, const int32_t* __restrict__ sbkt,
+                                           int nsuper, Fold&& fold) {
+  const int n_nodes = cnt->n_nodes;
+  const int m = (int)min((int64_t)nsuper, ((int64_t)n_nodes + kSuper * kChunk - 1) / (kSuper * kChunk));
+  int p = -1, kids[8];
+  auto read = [&](int L, int j) {
+    p = -1;
+    const int slot = L >= 0 && j < m ? sbkt[L * nsuper + j] : -1;
+    if (slot < 0) return;
+    p = obkt[slot];
+    for (int k = 0; k < 8; ++k) kids[k] = okids[8 * (int64_t)slot + k];
+  };
+  read(kLevels - 1, threadIdx.x);
+  for (int L = kLevels - 1; L >= 0; --L) {
+    if (p >= 0) fold(p, kids);
+    for (int j = threadIdx.x + kFinalThreads; j < m; j += kFinalThreads) {
+      read(L, j);
+      if (p >= 0) fold(p, kids);
+    }
+    read(L - 1, threadIdx.x);
+    __syncthreads();
+  }
+}
+
+__device__ __forceinline__ void fold_moments(int p, const int (&kids)[8], int n_nodes, Node* __restrict__ nodes,
+                                             Mom* __restrict__ mom) {
+  Mom c[8];
+  const double ctr[3] = {nodes[p].cx, nodes[p].cy, nodes[p].cz};
+  int n = 0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const bool ok = n == k && kids[k] > p && kids[k] < n_nodes;
+    if (ok) c[k] = mom[kids[k]];
+    n += ok ? 1 : 0;
+  }
+  Mom q{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+    if (k < n) add_mom(q, c[k]);
+  finish_node(p, q, ctr, nodes, mom);
+}
+
+__global__ __launch_bounds__(kSuperThreads) void k_moments_super(const Counts* __restrict__ cnt,
+                                                                 const int32_t* __restrict__ obkt,
+                                                                 const int32_t* __restrict__ nx, int nchunks,
+                                                                 Node* nodes, Mom* mom, int32_t* __restrict__ okids,
+                                                                 int32_t* __restrict__ sbkt, int nsuper) {
+  const int n_nodes = cnt->n_nodes;
+  if (threadIdx.x < kLevels) sbkt[threadIdx.x * nsuper + blockIdx.x] = -1;
+  __syncthreads();
+  fold_super(
+      cnt, obkt, nx, nchunks,
+      [&](int slot, int p, int (&kids)[8]) {
+        const int end = min(nx[p], n_nodes);
+        int c = p + 1;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          kids[k] = c < end ? c : -1;
+          if (c < end) c = max(nx[c], c + 1);
+          okids[8 * (int64_t)slot + k] = kids[k];
+        }
+      },
+      [&](int L, int slot) { sbkt[L * nsuper + blockIdx.x] = slot; },
+      [&](int p, const int (&kids)[8]) { fold_moments(p, kids, n_nodes, nodes, mom); });
+}
+
+__global__ __launch_bounds__(kFinalThreads) void k_moments_final(const Counts* __restrict__ cnt,
+                                                                 const int32_t* __restrict__ obkt,
+                                                                 const int32_t* __restrict__ okids,
+                                                                 const int32_t* __restrict__ sbkt, int nsuper,
+                                                                 Node* nodes, Mom* mom) {
+  const int n_nodes = cnt->n_nodes;
+  fold_final(cnt, obkt, okids, sbkt, nsuper,
+             [&](int p, const int (&kids)[8]) { fold_moments(p, kids, n_nodes, nodes, mom); });
 }
 
 // ---------------------------------------------------------------- driver
@@ -1177,10 +1272,11 @@ static hipError_t build_impl(const T* pos, const T* mass, int n, const BuildWs& 
   // internal nodes
   const int nch = (int)n_chunks(n);
   k_moments_chunk<<<nch, kChunkThreads, 0, st>>>(w.counts, w.nx, w.nlev, w.nodes, w.mom, w.obkt, nch);
-  k_open_kids<<<nblk((int64_t)kLevels * nch, 256), 256, 0, st>>>(w.counts, w.obkt, w.nx, nch, w.okids);
-  const int tg = nblk(nch, 256);
-  for (int L = kLevels - 1; L >= 0; --L)
-    k_moments_top<<<tg, 256, 0, st>>>(w.counts, w.obkt, w.okids, nch, w.nodes, w.mom, L);
+  const int nsup = n_super(n);
+  k_moments_super<<<nsup, kSuperThreads, 0, st>>>(w.counts, w.obkt, w.nx, nch, w.nodes, w.mom, w.okids, w.sbkt, nsup);
+  // (a node that straddles no workgroup's chunks is done)
+  if (nsup > 1)
+    k_moments_final<<<1, kFinalThreads, 0, st>>>(w.counts, w.obkt, w.okids, w.sbkt, nsup, w.nodes, w.mom);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (fork) return hipStreamWaitEvent(st, fork->join, 0);
   return hipSuccess;
@@ -1740,8 +1836,8 @@ __device__ __forceinline__ void quad_fold(double b[6], const double cb[6], doubl
   b[5] += cb[5] + m2 * d2;
 }
 
-// The two launches of the first moments (k_moments_chunk, k_moments_top), for
-// the second, over the same chunks: the chunk launch forms the leaves' moments
+// The launches of the first moments (k_moments_chunk, k_moments_super,
+// k_moments_final), for the second, over the same chunks: the chunk launch forms the leaves' moments
 // from their particles and folds the chunk's closed nodes in LDS; the
 // straddling nodes and their children are the lists the build made.
 template <typename T4>
@@ -1791,29 +1887,44 @@ __global__ __launch_bounds__(kChunkThreads) void k_quad_chunk(const Counts* __re
     if (!chunk_leaf(ci, c0, i) && ci.nx[i] <= c1) put_quad(qr, c0 + i, sb[i]);
 }
 
-__global__ __launch_bounds__(256) void k_quad_top(const Counts* __restrict__ cnt, const int32_t* __restrict__ obkt,
-                                                  const int32_t* __restrict__ okids, int nchunks,
-                                                  const Node* __restrict__ nodes, QuadRec* __restrict__ qr, int L) {
-  const int n_nodes = cnt->n_nodes;
-  {
-    const int m = min((n_nodes + kChunk - 1) / kChunk, nchunks);
-    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < m; j += gridDim.x * blockDim.x) {
-      const int slot = L * nchunks + j;
-      const int p = obkt[slot];
-      if (p < 0 || p >= n_nodes) continue;
-      const Node np = nodes[p];
-      double b[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-      for (int k = 0; k < 8; ++k) {
-        const int c = okids[8 * slot + k];
-        if (c <= p || c >= n_nodes) break;
-        const Node nc = nodes[c];
-        const QuadRec q = qr[c];
-        const double cb[6] = {q.bxx, q.bxy, q.bxz, q.byy, q.byz, q.bzz};
-        quad_fold(b, cb, nc.cx, nc.cy, nc.cz, nc.M, np.cx, np.cy, np.cz);
-      }
-      put_quad(qr, p, b);
-    }
+__device__ __forceinline__ void fold_quad(int p, const int (&kids)[8], int n_nodes, const Node* __restrict__ nodes,
+                                          QuadRec* qr) {
+  const double px = nodes[p].cx, py = nodes[p].cy, pz = nodes[p].cz;
+  double b[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int c = kids[k];
+    if (c <= p || c >= n_nodes) break;
+    const QuadRec q = qr[c];
+    const double cb[6] = {q.bxx, q.bxy, q.bxz, q.byy, q.byz, q.bzz};
+    quad_fold(b, cb, nodes[c].cx, nodes[c].cy, nodes[c].cz, nodes[c].M, px, py, pz);
   }
+  put_quad(qr, p, b);
+}
+
+__global__ __launch_bounds__(kSuperThreads) void k_quad_super(const Counts* __restrict__ cnt,
+                                                              const int32_t* __restrict__ obkt,
+                                                              const int32_t* __restrict__ nx, int nchunks,
+                                                              const Node* __restrict__ nodes,
+                                                              const int32_t* __restrict__ okids, QuadRec* qr) {
+  const int n_nodes = cnt->n_nodes;
+  fold_super(
+      cnt, obkt, nx, nchunks,
+      [&](int slot, int, int (&kids)[8]) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) kids[k] = okids[8 * (int64_t)slot + k];
+      },
+      [](int, int) {}, [&](int p, const int (&kids)[8]) { fold_quad(p, kids, n_nodes, nodes, qr); });
+}
+
+__global__ __launch_bounds__(kFinalThreads) void k_quad_final(const Counts* __restrict__ cnt,
+                                                              const int32_t* __restrict__ obkt,
+                                                              const int32_t* __restrict__ okids,
+                                                              const int32_t* __restrict__ sbkt, int nsuper,
+                                                              const Node* __restrict__ nodes, QuadRec* qr) {
+  const int n_nodes = cnt->n_nodes;
+  fold_final(cnt, obkt, okids, sbkt, nsuper,
+             [&](int p, const int (&kids)[8]) { fold_quad(p, kids, n_nodes, nodes, qr); });
 }
 
 template <typename T4>
@@ -1822,9 +1933,10 @@ static hipError_t quad_impl(int n, const BuildWs& w, hipStream_t st) {
   const int nch = (int)n_chunks(n);
   k_quad_chunk<T4><<<nch, kChunkThreads, 0, st>>>(w.counts, w.nx, w.nlev, w.nodes, reinterpret_cast<const T4*>(w.ps),
                                                   w.qrec);
-  const int tg = nblk(nch, 256);
-  for (int L = kLevels - 1; L >= 0; --L)
-    k_quad_top<<<tg, 256, 0, st>>>(w.counts, w.obkt, w.okids, nch, w.nodes, w.qrec, L);
+  const int nsup = n_super(n);
+  k_quad_super<<<nsup, kSuperThreads, 0, st>>>(w.counts, w.obkt, w.nx, nch, w.nodes, w.okids, w.qrec);
+  if (nsup > 1)
+    k_quad_final<<<1, kFinalThreads, 0, st>>>(w.counts, w.obkt, w.okids, w.sbkt, nsup, w.nodes, w.qrec);
   return hipGetLastError();
 }
 

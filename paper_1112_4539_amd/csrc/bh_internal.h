@@ -33,7 +33,9 @@ struct alignas(32) Mom {
 // in kLevels x (number of chunks) slots, each with its children.
 constexpr int kChunk = 512;
 constexpr int kChunkThreads = 256;  // workgroup of the chunk launches: kChunk / kChunkThreads nodes per thread
+constexpr int kSuperChunks = 32;    // chunks of one workgroup of the straddling nodes' first launch
 inline int64_t n_chunks(int64_t n) { return (2 * (n > 0 ? n : 1) + kChunk - 1) / kChunk; }
+inline int n_super(int64_t n) { return (int)((n_chunks(n) + kSuperChunks - 1) / kSuperChunks); }
 
 // Runs of a cluster's subtree: a walk sums a target's terms run by run (equally
 // many preorder nodes each) and adds the runs' sums in order.  Several waves can
@@ -90,6 +92,7 @@ struct BuildWs {
   uint8_t* nlev;            // [2n] level of every node, for the moment passes
   int32_t* obkt;            // [kLevels][n_chunks] the straddling node of each level and chunk, or -1
   int32_t* okids;           // [kLevels][n_chunks][8] their children in octant order, -1 after the last
+  int32_t* sbkt;            // [kLevels][n_super] the slot that straddles the end of kSuperChunks chunks, or -1
   int32_t* anc;             // [K][kMaxRuns][kAncSlots] ancestors of each run's first node by level, -1 none (null: K > kAncClusters)
   WalkNode* wnodes;         // [2n] walk copy of the nodes for the last uniform theta
   int32_t* horder;          // [n] Morton positions in the Hilbert walk order (filled on demand)

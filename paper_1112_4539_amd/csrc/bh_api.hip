@@ -75,10 +75,8 @@ size_t up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 size_t layout(int64_t n, int64_t K, int prec, char* base, bh::BuildWs* w, int32_t** rank, int32_t** queue) {
   const size_t N = (size_t)(n > 0 ? n : 1);
   const size_t nodes = 2 * N;
-  const size_t sort_tiles = (N + bh::kSortTile - 1) / bh::kSortTile;
-  const size_t hist = 256 * sort_tiles;
-  const size_t max_scan = hist > N + 1 ? hist : N + 1;
-  const size_t scan_tiles = (max_scan + bh::kScanTile - 1) / bh::kScanTile + 16;
+  const size_t words = 2 * 256 * (size_t)bh::sort_tiles((int64_t)N);
+  const size_t scan_tiles = (N + 1 + bh::kScanTile - 1) / bh::kScanTile + 16;
   const size_t ps = (prec == BH_FP64 ? 32 : 16) * N;
   size_t off = 0;
   auto take = [&](size_t bytes) -> char* {
@@ -104,7 +102,9 @@ size_t layout(int64_t n, int64_t K, int prec, char* base, bh::BuildWs* w, int32_
   t.ukey = reinterpret_cast<uint64_t*>(take(8 * N));
   t.idx_a = reinterpret_cast<int32_t*>(take(4 * N));
   t.idx_b = reinterpret_cast<int32_t*>(take(4 * N));
-  t.hist = reinterpret_cast<int32_t*>(take(4 * hist));
+  t.hist = reinterpret_cast<int32_t*>(take(4 * 256 * bh::kSortPasses));
+  t.ticket = reinterpret_cast<int32_t*>(take(4 * bh::kSortPasses));
+  t.tiles = reinterpret_cast<uint32_t*>(take(4 * words));
   t.scan_tiles = reinterpret_cast<int32_t*>(take(4 * scan_tiles));
   t.ps = take(ps);
   t.flag = reinterpret_cast<int32_t*>(take(4 * N));
@@ -136,8 +136,9 @@ size_t layout(int64_t n, int64_t K, int prec, char* base, bh::BuildWs* w, int32_
   t.hkey_a = reinterpret_cast<uint64_t*>(take(8 * N));
   t.hkey_b = reinterpret_cast<uint64_t*>(take(8 * N));
   t.hidx = reinterpret_cast<int32_t*>(take(4 * N));
-  t.hhist = reinterpret_cast<int32_t*>(take(4 * hist));
-  t.hscan = reinterpret_cast<int32_t*>(take(4 * scan_tiles));
+  t.hhist = reinterpret_cast<int32_t*>(take(4 * 256 * bh::kSortPasses));
+  t.hticket = reinterpret_cast<int32_t*>(take(4 * bh::kSortPasses));
+  t.htiles = reinterpret_cast<uint32_t*>(take(4 * words));
   t.qrec = reinterpret_cast<bh::QuadRec*>(take(sizeof(bh::QuadRec) * (nodes + 1)));
   int32_t* r = reinterpret_cast<int32_t*>(take(4 * N));
   if (w) *w = t;

@@ -263,13 +263,6 @@ __global__ __launch_bounds__(256) void k_seg_check(const int64_t* __restrict__ o
   if (bad) atomicOr(&cnt->bad_input, 2);
 }
 
-__global__ void k_single_off(int64_t* __restrict__ off, int64_t n) {
-  if (threadIdx.x == 0) {
-    off[0] = 0;
-    off[1] = n;
-  }
-}
-
 __device__ __forceinline__ int64_t clamp_off(int64_t v, int64_t n) { return v < 0 ? 0 : (v > n ? n : v); }
 
 // Cluster of caller index i: the k with off[k] <= i < off[k+1] (off in global
@@ -362,18 +355,6 @@ __device__ __forceinline__ uint64_t morton_key(const Cube& cube, const T* __rest
   return (spread3(q[0]) << 2) | (spread3(q[1]) << 1) | spread3(q[2]);
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_keys(const T* __restrict__ pos, int n, const Cube* __restrict__ cubes,
-                                              const int64_t* __restrict__ off, int K, int32_t* __restrict__ seg,
-                                              uint64_t* __restrict__ keys, int32_t* __restrict__ idx) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int k = K > 1 ? seg_of(off, K, i) : 0;
-  if (seg) seg[i] = k;
-  keys[i] = morton_key(cubes[k], pos, i);
-  idx[i] = i;
-}
-
 // ---------------------------------------------------------------- radix sort
 // Digit sources of a pass: 8 bits of the key, or 8 bits of the item's cluster.
 // The cluster of caller index v is a search over the cluster offsets, staged in
@@ -400,108 +381,74 @@ struct SegTable {
   }
 };
 
-template <int kDig>
-__global__ __launch_bounds__(kSortThreads) void k_rs_hist(const uint64_t* __restrict__ keys,
-                                                          const int32_t* __restrict__ vals,
-                                                          const int32_t* __restrict__ seg,
-                                                          const int64_t* __restrict__ seg_off, int K, int n,
-                                                          int shift, int32_t* __restrict__ hist, int ntiles) {
-  __shared__ uint32_t h[256];
-  __shared__ SegTable<kDig> tab;
-  h[threadIdx.x] = 0;
-  tab.load(seg_off, K);
-  __syncthreads();
-  int64_t base = (int64_t)blockIdx.x * kSortTile;
-#pragma unroll 4
-  for (int r = 0; r < kSortItems; ++r) {
-    int64_t i = base + r * kSortThreads + threadIdx.x;
-    if (i < n) atomicAdd(&h[tab.digit(kDig == kDigKey ? keys[i] : 0ull, kDig == kDigKey ? 0 : vals[i], seg, K, shift)], 1u);
-  }
-  __syncthreads();
-  hist[(int64_t)threadIdx.x * ntiles + blockIdx.x] = (int32_t)h[threadIdx.x];
-}
+// One launch per pass.  A workgroup takes the next tile (a ticket, so that tiles
+// start in order), counts its digits, and learns how many items of each digit
+// the tiles before it hold by looking back over what they have published: per
+// tile and digit a word with the tile's own count or, once known, the count of
+// all tiles up to it ("decoupled look-back", Merrill & Garland 2016).  A word
+// carries its own state, so it needs no fence; a tile waits only for tiles that
+// started before it.  Where each digit starts comes from the histograms that
+// the key kernel has added up for all passes.
+//
+// The scatter is stable and goes through LDS.  Each wave takes a contiguous
+// quarter of the tile and ranks its items in input order (the rank among equal
+// digits within 64 items comes from 8 ballots, one per digit bit); the items
+// are placed in LDS sorted by digit, and the tile then leaves in that order, so
+// that consecutive lanes write consecutive addresses of one digit's run instead
+// of 8- and 4-byte pieces all over the output.
+//
+// A pass moves 24 bytes per particle and, for small sets, is one tile's latency:
+// smaller tiles for those, so that more CUs take part (sort_items).  (As a
+// histogram, two scan kernels and a scatter a pass took 33 us for 100,000
+// particles, 49 for 1M and 64 for 4M; it takes 10, 23 and 54, the digit counts of
+// the key kernel 5 more in all, 25 at 4M.)
+constexpr uint32_t kTileCount = 1u << 30, kTileTotal = 2u << 30, kTileMask = kTileCount - 1;
 
-// Stable scatter through LDS.  Each wave takes a contiguous quarter of the
-// tile and ranks its items in input order (the rank among equal digits within
-// 64 items comes from 8 ballots, one per digit bit), after per-wave digit
-// counts have given every wave its starting slot per digit; the items are
-// placed in LDS sorted by digit, and the tile then leaves in that order, so
-// that consecutive lanes write consecutive addresses of one digit's run
-// instead of 8- and 4-byte pieces all over the output.
-template <int kDig>
-__global__ __launch_bounds__(kSortThreads) void k_rs_scatter(const uint64_t* __restrict__ kin,
-                                                             const int32_t* __restrict__ vin,
-                                                             const int32_t* __restrict__ seg,
-                                                             const int64_t* __restrict__ seg_off, int K,
-                                                             uint64_t* __restrict__ kout,
-                                                             int32_t* __restrict__ vout, int n, int shift,
-                                                             const int32_t* __restrict__ offs, int ntiles) {
+template <int kDig, int kItems>
+__global__ __launch_bounds__(kSortThreads) void k_rs_pass(const uint64_t* __restrict__ kin,
+                                                          const int32_t* __restrict__ vin,
+                                                          const int32_t* __restrict__ seg,
+                                                          const int64_t* __restrict__ seg_off, int K,
+                                                          uint64_t* __restrict__ kout, int32_t* __restrict__ vout, int n,
+                                                          int shift, const int32_t* __restrict__ hist,
+                                                          uint32_t* tiles, uint32_t* __restrict__ tiles_next,
+                                                          int32_t* __restrict__ ticket, int ntiles) {
   constexpr int kWaves = kSortThreads / 64;
-  constexpr int kPerWave = kSortTile / kWaves;
-  __shared__ uint64_t lkey[kSortTile];
-  __shared__ int32_t lval[kSortTile];
-  __shared__ uint8_t ldig[kSortTile];
-  __shared__ uint32_t goff[256];          // output position of the tile's first item of each digit
-  __shared__ uint32_t loff[256];          // tile position of the first item of each digit
-  __shared__ uint32_t wslot[kWaves][256]; // per wave: its counts, then its next slot per digit
-  __shared__ uint32_t wsum[kWaves];
+  constexpr int kTile = kSortThreads * kItems;
+  constexpr int kPerWave = kTile / kWaves;
+  __shared__ uint64_t lkey[kTile];
+  __shared__ int32_t lval[kTile];
+  __shared__ uint8_t ldig[kTile];
+  __shared__ uint32_t goff[256];           // output position of the tile's first item of each digit
+  __shared__ uint32_t loff[256];           // tile position of the first item of each digit
+  __shared__ uint32_t wslot[kWaves][256];  // per wave: its counts, then its first slot per digit
+  __shared__ int scan[kWaves];
   __shared__ SegTable<kDig> tab;
+  __shared__ int tile_s;
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
-  const int64_t tile0 = (int64_t)blockIdx.x * kSortTile;
-  const int m = (int)min((int64_t)kSortTile, (int64_t)n - tile0);  // items in this tile
-  goff[t] = (uint32_t)offs[(int64_t)t * ntiles + blockIdx.x];
+  if (t == 0) tile_s = atomicAdd(ticket, 1);
 #pragma unroll
   for (int k = 0; k < kWaves; ++k) wslot[k][t] = 0;
   tab.load(seg_off, K);
   __syncthreads();
-  // per-wave digit counts
-  for (int r = 0; r < kPerWave / 64; ++r) {
+  const int tile = tile_s;
+  if (tile >= ntiles) return;
+  const int64_t tile0 = (int64_t)tile * kTile;
+  const int m = (int)min((int64_t)kTile, (int64_t)n - tile0);  // items in this tile
+  uint64_t key[kItems];
+  int32_t val[kItems];
+  uint32_t at[kItems];  // digit << 16 | rank among the wave's items of that digit
+#pragma unroll
+  for (int r = 0; r < kItems; ++r) {
     const int j = w * kPerWave + r * 64 + lane;
-    if (j < m) {
-      const int64_t i = tile0 + j;
-      atomicAdd(&wslot[w][tab.digit(kDig == kDigKey ? kin[i] : 0ull, kDig == kDigKey ? 0 : vin[i], seg, K, shift)], 1u);
-    }
+    key[r] = j < m ? kin[tile0 + j] : 0ull;
+    val[r] = j < m ? vin[tile0 + j] : 0;
   }
-  __syncthreads();
-  {
-    // digit t: tile total, exclusive scan over digits, then each wave's first slot
-    uint32_t cw[kWaves];
-    uint32_t c = 0;
-#pragma unroll
-    for (int k = 0; k < kWaves; ++k) {
-      cw[k] = wslot[k][t];
-      c += cw[k];
-    }
-    uint32_t x = c;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t y = __shfl_up(x, o, 64);
-      if (lane >= o) x += y;
-    }
-    if (lane == 63) wsum[w] = x;
-    __syncthreads();
-    uint32_t before = 0;
-    for (int k = 0; k < w; ++k) before += wsum[k];
-    const uint32_t first = before + x - c;
-    loff[t] = first;
-    uint32_t run = first;
-#pragma unroll
-    for (int k = 0; k < kWaves; ++k) {
-      wslot[k][t] = run;
-      run += cw[k];
-    }
-  }
-  __syncthreads();
-  // each wave places its items in input order; the slots it advances are its own
   const uint64_t lt = (1ull << lane) - 1ull;
-  const uint64_t le = lt | (1ull << lane);
-  for (int r = 0; r < kPerWave / 64; ++r) {
-    const int j = w * kPerWave + r * 64 + lane;
-    const bool valid = j < m;
-    const int64_t i = tile0 + j;
-    const uint64_t key = valid ? kin[i] : 0ull;
-    const int32_t val = valid ? vin[i] : 0;
-    const uint32_t d = valid ? tab.digit(key, val, seg, K, shift) : 0u;
+#pragma unroll
+  for (int r = 0; r < kItems; ++r) {
+    const bool valid = w * kPerWave + r * 64 + lane < m;
+    const uint32_t d = valid ? tab.digit(key[r], val[r], seg, K, shift) : 0u;
     uint64_t peers = ballot(valid);
 #pragma unroll
     for (int b = 0; b < 8; ++b) {
@@ -509,19 +456,73 @@ __global__ __launch_bounds__(kSortThreads) void k_rs_scatter(const uint64_t* __r
       const uint64_t mk = ballot(bit);
       peers &= bit ? mk : ~mk;
     }
-    if (valid) {
-      const uint32_t q = wslot[w][d] + (uint32_t)__popcll(peers & lt);
-      lkey[q] = key;
-      lval[q] = val;
-      ldig[q] = (uint8_t)d;
-    }
-    // (the wave's LDS operations take effect in program order: every lane has
-    // read its slot above before the last lane of each digit advances it)
-    if (valid && (peers & ~le) == 0ull) wslot[w][d] += (uint32_t)__popcll(peers);
+    const int leader = valid ? __builtin_ctzll(peers) : lane;
+    uint32_t base = 0;
+    if (valid && lane == leader) base = atomicAdd(&wslot[w][d], (uint32_t)__popcll(peers));
+    at[r] = d << 16 | (__shfl(base, leader, 64) + (uint32_t)__popcll(peers & lt));
   }
   __syncthreads();
+  // digit t: the tile's count, published for the tiles after this one
+  uint32_t cw[kWaves], c = 0;
+#pragma unroll
+  for (int k = 0; k < kWaves; ++k) c += cw[k] = wslot[k][t];
+  uint32_t* mine = tiles + (int64_t)tile * 256 + t;
+  __hip_atomic_store(mine, (tile == 0 ? kTileTotal : kTileCount) | c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  tiles_next[(int64_t)tile * 256 + t] = 0;
+  // each digit's first position in the tile and in the output, each wave's first slot
+  int tot;
+  const uint32_t first = (uint32_t)block_excl_scan<kSortThreads>((int)c, scan, &tot);
+  const uint32_t digit0 = (uint32_t)block_excl_scan<kSortThreads>(hist[t], scan, &tot);
+  loff[t] = first;
+  uint32_t run = first;
+#pragma unroll
+  for (int k = 0; k < kWaves; ++k) {
+    wslot[k][t] = run;
+    run += cw[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kItems; ++r) {
+    if (w * kPerWave + r * 64 + lane < m) {
+      const uint32_t d = at[r] >> 16, q = wslot[w][d] + (at[r] & 0xffffu);
+      lkey[q] = key[r];
+      lval[q] = val[r];
+      ldig[q] = (uint8_t)d;
+    }
+  }
+  // look back, kBack tiles at a time
+  constexpr int kBack = 8;
+  uint32_t before = 0;
+  for (int p = tile - 1; p >= 0;) {
+    uint32_t word[kBack];
+#pragma unroll
+    for (int k = 0; k < kBack; ++k)
+      word[k] = p - k >= 0 ? __hip_atomic_load(tiles + (int64_t)(p - k) * 256 + t, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT)
+                           : 0u;
+    bool open = true;  // no tile without a word met yet
+#pragma unroll
+    for (int k = 0; k < kBack; ++k) {
+      if (!open) continue;
+      if (word[k] == 0u) {
+        open = false;
+      } else {
+        before += word[k] & kTileMask;
+        --p;
+        if (word[k] & kTileTotal) {
+          p = -1;
+          open = false;
+        }
+      }
+    }
+    if (p >= 0 && !open) __builtin_amdgcn_s_sleep(1);
+  }
+  if (tile > 0) __hip_atomic_store(mine, kTileTotal | (before + c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  goff[t] = digit0 + before;
+  __syncthreads();
   // the tile in digit order: position j holds the (j - loff[d])-th item of digit d
-  for (int r = 0; r < kSortItems; ++r) {
+#pragma unroll
+  for (int r = 0; r < kItems; ++r) {
     const int j = r * kSortThreads + t;
     if (j < m) {
       const uint32_t d = ldig[j];
@@ -530,6 +531,74 @@ __global__ __launch_bounds__(kSortThreads) void k_rs_scatter(const uint64_t* __r
       vout[q] = lval[j];
     }
   }
+}
+
+// Adds the digits of one item to the histograms of all passes in LDS
+// (h [kSortPasses][256]): key digits, then cluster digits.
+__device__ __forceinline__ void count_digits(uint32_t (*h)[256], uint64_t key, int key_passes, uint32_t cluster,
+                                             int seg_passes) {
+  for (int p = 0; p < key_passes; ++p) atomicAdd(&h[p][(uint32_t)(key >> (8 * p)) & 255u], 1u);
+  for (int p = 0; p < seg_passes; ++p) atomicAdd(&h[key_passes + p][(cluster >> (8 * p)) & 255u], 1u);
+}
+__device__ __forceinline__ void clear_digits(uint32_t (*h)[256], int passes) {
+  for (int k = threadIdx.x; k < passes * 256; k += blockDim.x) h[0][k] = 0;
+  __syncthreads();
+}
+__device__ __forceinline__ void store_digits(uint32_t (*h)[256], int passes, int32_t* __restrict__ hist) {
+  __syncthreads();
+  for (int k = threadIdx.x; k < passes * 256; k += blockDim.x)
+    if (h[0][k]) atomicAdd(&hist[k], (int32_t)h[0][k]);
+}
+
+// Workgroups of a key kernel: each ends with an atomic per digit and pass, so
+// few large ones.
+constexpr int kKeyThreads = 512;
+static inline int key_blocks(int64_t n) { return (int)min((int64_t)512, max((int64_t)1, (n + 2047) / 2048)); }
+
+// What a sort needs beside its keys: the passes' histograms and tickets, and two
+// tables of tile words, which the passes use in turn (each clears the other's
+// for the next one).
+struct SortScratch {
+  int32_t* hist;     // [kSortPasses][256]
+  int32_t* ticket;   // [kSortPasses]
+  uint32_t* tiles[2];
+};
+
+template <int kDig>
+static void launch_pass(const uint64_t* kin, const int32_t* vin, const BuildWs& w, uint64_t* kout, int32_t* vout, int n,
+                        int shift, const SortScratch& sc, int pass, hipStream_t st) {
+  const int items = sort_items(n);
+  const int ntiles = (int)sort_tiles(n);
+  auto go = [&](auto kernel) {
+    kernel<<<ntiles, kSortThreads, 0, st>>>(kin, vin, w.seg, w.seg_off, w.n_seg, kout, vout, n, shift,
+                                            sc.hist + 256 * pass, sc.tiles[pass & 1], sc.tiles[(pass & 1) ^ 1],
+                                            sc.ticket + pass, ntiles);
+  };
+  if (items == 4)
+    go(k_rs_pass<kDig, 4>);
+  else if (items == 8)
+    go(k_rs_pass<kDig, 8>);
+  else
+    go(k_rs_pass<kDig, 16>);
+}
+
+template <typename T>
+__global__ __launch_bounds__(kKeyThreads) void k_keys(const T* __restrict__ pos, int n, const Cube* __restrict__ cubes,
+                                                      const int64_t* __restrict__ off, int K, int seg_passes,
+                                                      int32_t* __restrict__ seg, uint64_t* __restrict__ keys,
+                                                      int32_t* __restrict__ idx, int32_t* __restrict__ hist) {
+  __shared__ uint32_t h[kSortPasses][256];
+  const int passes = 8 + seg_passes;
+  clear_digits(h, passes);
+  for (int64_t i = (int64_t)blockIdx.x * kKeyThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kKeyThreads) {
+    const int k = K > 1 ? seg_of(off, K, i) : 0;
+    if (seg) seg[i] = k;
+    const uint64_t key = morton_key(cubes[k], pos, (int)i);
+    keys[i] = key;
+    idx[i] = (int32_t)i;
+    count_digits(h, key, 8, (uint32_t)k, seg_passes);
+  }
+  store_digits(h, passes, hist);
 }
 
 __global__ __launch_bounds__(256) void k_copy_kv(const uint64_t* __restrict__ kin, const int32_t* __restrict__ vin,
@@ -575,9 +644,17 @@ __global__ __launch_bounds__(256) void k_unique_write(const uint64_t* __restrict
                                                       const int32_t* __restrict__ flag,
                                                       const int32_t* __restrict__ uid,
                                                       uint64_t* __restrict__ ukey, int32_t* __restrict__ ustart,
-                                                      int32_t* __restrict__ ucid, Counts* __restrict__ cnt) {
+                                                      int32_t* __restrict__ ucid, Counts* __restrict__ cnt,
+                                                      int32_t* __restrict__ nstart, uint32_t* __restrict__ lmask) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
+  // (cleared here for k_internal_write)
+  nstart[i] = 0;
+  lmask[i] = 0;
+  if (i == n - 1) {
+    nstart[n] = 0;
+    lmask[n] = 0;
+  }
   if (flag[i]) {
     ukey[uid[i]] = keys[i];
     ustart[uid[i]] = i;
@@ -1182,21 +1259,44 @@ static inline int nblk(int64_t n, int t) { return (int)((n + t - 1) / t) > 0 ? (
 template <typename T4>
 static hipError_t hilbert_impl(int n, const BuildWs& w, hipStream_t st);
 
+__device__ __forceinline__ void clear_sort(int32_t* __restrict__ hist, int32_t* __restrict__ ticket,
+                                           uint32_t* __restrict__ tiles, int64_t words) {
+  const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = i0; i < kSortPasses * 256; i += step) hist[i] = 0;
+  if (i0 < kSortPasses) ticket[i0] = 0;
+  for (int64_t i = i0; i < words; i += step) tiles[i] = 0;
+}
+
+__global__ __launch_bounds__(256) void k_clear_sort(int32_t* __restrict__ hist, int32_t* __restrict__ ticket,
+                                                    uint32_t* __restrict__ tiles, int64_t words) {
+  clear_sort(hist, ticket, tiles, words);
+}
+
+__global__ __launch_bounds__(256) void k_init(BuildWs w, SortScratch sc, int64_t n, int64_t words, int64_t n_anc) {
+  const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+  if (i0 < (int64_t)(sizeof(Counts) / 4)) reinterpret_cast<int32_t*>(w.counts)[i0] = 0;
+  if (w.seg_off == w.own_off && i0 < 2) w.own_off[i0] = i0 ? n : 0;
+  for (int64_t i = i0; i <= w.n_seg; i += step) w.croot[i] = 0;
+  for (int64_t i = i0; i < n_anc; i += step) w.anc[i] = -1;
+  if (words) clear_sort(sc.hist, sc.ticket, sc.tiles[0], words);
+}
+
+static inline int clear_blocks(int64_t n) { return (int)min((int64_t)1024, max((int64_t)8, n / 4096)); }
+
 template <typename T, typename T4>
 static hipError_t build_impl(const T* pos, const T* mass, int n, const BuildWs& w, const BuildFork* fork,
                              hipStream_t st) {
   hipError_t e;
   const int K = w.n_seg;
-  k_fill_i32<<<1, 64, 0, st>>>(reinterpret_cast<int32_t*>(w.counts), sizeof(Counts) / 4, 0);
-  if (w.seg_off == w.own_off) k_single_off<<<1, 64, 0, st>>>(w.own_off, n);
-  k_seg_check<<<nblk(K + 1, 256), 256, 0, st>>>(w.seg_off, K, n, w.counts);
-  // cluster roots for an empty build: every cluster starts and ends at node 0
-  k_fill_i32<<<nblk(K + 1, 256), 256, 0, st>>>(w.croot, K + 1, 0);
-  if (n == 0) return hipGetLastError();
-  if (w.anc) {
-    const int64_t na = (int64_t)K * kMaxRuns * kAncSlots;
-    k_fill_i32<<<nblk(na, 256), 256, 0, st>>>(w.anc, na, -1);
+  // counters, offsets, the sort's words, run ancestors, and cluster roots for an
+  // empty build (every cluster starts and ends at node 0)
+  {
+    const SortScratch sc{w.hist, w.ticket, {w.tiles, nullptr}};
+    k_init<<<clear_blocks(n), 256, 0, st>>>(w, sc, n, n > 0 ? 256 * sort_tiles(n) : 0,
+                                            w.anc ? (int64_t)K * kMaxRuns * kAncSlots : 0);
   }
+  if (w.seg_off != w.own_off) k_seg_check<<<nblk(K + 1, 256), 256, 0, st>>>(w.seg_off, K, n, w.counts);
+  if (n == 0) return hipGetLastError();
   // root cubes
   if (K == 1) {
     const int nbb = w.n_bbox_blocks;
@@ -1210,32 +1310,20 @@ static hipError_t build_impl(const T* pos, const T* mass, int n, const BuildWs& 
   int32_t* seg = K > 1 ? w.seg : nullptr;
   int32_t* scid = K > 1 ? w.scid : nullptr;
   int32_t* ucid = K > 1 ? w.ucid : nullptr;
-  k_keys<T><<<nblk(n, 256), 256, 0, st>>>(pos, n, w.cube, w.seg_off, K, seg, w.key_a, w.idx_a);
-  const int ntiles = (n + kSortTile - 1) / kSortTile;
   int seg_passes = 0;
   for (unsigned r = (unsigned)(K - 1); r; r >>= 8) ++seg_passes;
+  const SortScratch sc{w.hist, w.ticket, {w.tiles, w.tiles + 256 * sort_tiles(n)}};
+  k_keys<T><<<key_blocks(n), kKeyThreads, 0, st>>>(pos, n, w.cube, w.seg_off, K, seg_passes, seg, w.key_a, w.idx_a,
+                                                   w.hist);
   uint64_t *kin = w.key_a, *kout = w.key_b;
   int32_t *vin = w.idx_a, *vout = w.idx_b;
-  const bool seg_lds = K + 1 <= kSegLds;
   for (int pass = 0; pass < 8 + seg_passes; ++pass) {
-    const bool segp = pass >= 8;
-    const int shift = segp ? 8 * (pass - 8) : 8 * pass;
-    if (!segp)
-      k_rs_hist<kDigKey><<<ntiles, kSortThreads, 0, st>>>(kin, vin, w.seg, w.seg_off, K, n, shift, w.hist, ntiles);
-    else if (seg_lds)
-      k_rs_hist<kDigSegLds><<<ntiles, kSortThreads, 0, st>>>(kin, vin, w.seg, w.seg_off, K, n, shift, w.hist, ntiles);
+    if (pass < 8)
+      launch_pass<kDigKey>(kin, vin, w, kout, vout, n, 8 * pass, sc, pass, st);
+    else if (K + 1 <= kSegLds)
+      launch_pass<kDigSegLds>(kin, vin, w, kout, vout, n, 8 * (pass - 8), sc, pass, st);
     else
-      k_rs_hist<kDigSegIdx><<<ntiles, kSortThreads, 0, st>>>(kin, vin, w.seg, w.seg_off, K, n, shift, w.hist, ntiles);
-    if ((e = scan_excl(w.hist, w.hist, 256 * ntiles, w.scan_tiles, nullptr, st)) != hipSuccess) return e;
-    if (!segp)
-      k_rs_scatter<kDigKey><<<ntiles, kSortThreads, 0, st>>>(kin, vin, w.seg, w.seg_off, K, kout, vout, n, shift,
-                                                             w.hist, ntiles);
-    else if (seg_lds)
-      k_rs_scatter<kDigSegLds><<<ntiles, kSortThreads, 0, st>>>(kin, vin, w.seg, w.seg_off, K, kout, vout, n, shift,
-                                                                w.hist, ntiles);
-    else
-      k_rs_scatter<kDigSegIdx><<<ntiles, kSortThreads, 0, st>>>(kin, vin, w.seg, w.seg_off, K, kout, vout, n, shift,
-                                                                w.hist, ntiles);
+      launch_pass<kDigSegIdx>(kin, vin, w, kout, vout, n, 8 * (pass - 8), sc, pass, st);
     uint64_t* tk = kin; kin = kout; kout = tk;
     int32_t* tv = vin; vin = vout; vout = tv;
   }
@@ -1252,13 +1340,11 @@ static hipError_t build_impl(const T* pos, const T* mass, int n, const BuildWs& 
   k_unique_flags<<<nblk(n, 256), 256, 0, st>>>(w.key_a, scid, n, w.flag);
   if ((e = scan_excl(w.flag, w.uid, n, w.scan_tiles, nullptr, st)) != hipSuccess) return e;
   k_unique_write<<<nblk(n, 256), 256, 0, st>>>(w.key_a, scid, n, w.flag, w.uid, w.ukey, w.ustart, ucid,
-                                               w.counts);
+                                               w.counts, w.nstart, w.lmask);
   k_croot_first<<<nblk(K + 1, 256), 256, 0, st>>>(w.seg_off, K, n, w.uid, w.counts, w.croot);
   // internal nodes
   k_pairs<<<nblk(n, 256), 256, 0, st>>>(w.ukey, ucid, w.counts, w.split, w.flag, w.pf, w.pl, n);
   if ((e = scan_excl(w.flag, w.uid, n, w.scan_tiles, nullptr, st)) != hipSuccess) return e;
-  k_fill_i32<<<nblk(n + 1, 256), 256, 0, st>>>(w.nstart, n + 1, 0);
-  k_fill_i32<<<nblk(n + 1, 256), 256, 0, st>>>(reinterpret_cast<int32_t*>(w.lmask), n + 1, 0);
   k_internal_write<<<nblk(n, 256), 256, 0, st>>>(w.flag, w.uid, w.split, w.pf, w.pl, w.counts, w.ilevel, w.ifirst,
                                                  w.ilast, w.nstart, w.lmask, n);
   if ((e = scan_excl(w.nstart, w.nexcl, n + 1, w.scan_tiles, nullptr, st)) != hipSuccess) return e;
@@ -1370,14 +1456,20 @@ __device__ __forceinline__ uint32_t hilbert_key(const Cube& cube, const T4& p, i
 }
 
 template <typename T4>
-__global__ __launch_bounds__(256) void k_hkeys(const T4* __restrict__ ps, int n, const Cube* __restrict__ cubes,
-                                               const int32_t* __restrict__ scid, int levels,
-                                               uint64_t* __restrict__ keys, int32_t* __restrict__ idx) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n) return;
-  const int cl = scid ? scid[k] : 0;
-  keys[k] = ((uint64_t)(uint32_t)cl << (3 * levels)) | hilbert_key(cubes[cl], ps[k], levels);
-  idx[k] = k;
+__global__ __launch_bounds__(kKeyThreads) void k_hkeys(const T4* __restrict__ ps, int n, const Cube* __restrict__ cubes,
+                                                       const int32_t* __restrict__ scid, int levels, int passes,
+                                                       uint64_t* __restrict__ keys, int32_t* __restrict__ idx,
+                                                       int32_t* __restrict__ hist) {
+  __shared__ uint32_t h[kSortPasses][256];
+  clear_digits(h, passes);
+  for (int64_t k = (int64_t)blockIdx.x * kKeyThreads + threadIdx.x; k < n; k += (int64_t)gridDim.x * kKeyThreads) {
+    const int cl = scid ? scid[k] : 0;
+    const uint64_t key = ((uint64_t)(uint32_t)cl << (3 * levels)) | hilbert_key(cubes[cl], ps[k], levels);
+    keys[k] = key;
+    idx[k] = (int32_t)k;
+    count_digits(h, key, passes, 0u, 0);
+  }
+  store_digits(h, passes, hist);
 }
 
 template <typename T4>
@@ -1386,17 +1478,16 @@ static hipError_t hilbert_impl(int n, const BuildWs& w, hipStream_t st) {
   const int K = w.n_seg;
   const int levels = hilbert_levels(K);
   const int passes = (3 * levels + bits_of((unsigned)(K - 1)) + 7) / 8;
-  k_hkeys<T4><<<nblk(n, 256), 256, 0, st>>>(reinterpret_cast<const T4*>(w.ps), n, w.cube, K > 1 ? w.scid : nullptr,
-                                            levels, w.hkey_a, w.horder);
-  const int ntiles = (n + kSortTile - 1) / kSortTile;
+  const SortScratch sc{w.hhist, w.hticket, {w.htiles, w.htiles + 256 * sort_tiles(n)}};
+  // (formed once per build, beside it or later: its words are cleared here)
+  k_clear_sort<<<clear_blocks(n), 256, 0, st>>>(sc.hist, sc.ticket, sc.tiles[0], 256 * sort_tiles(n));
+  k_hkeys<T4><<<key_blocks(n), kKeyThreads, 0, st>>>(reinterpret_cast<const T4*>(w.ps), n, w.cube,
+                                                     K > 1 ? w.scid : nullptr, levels, passes, w.hkey_a, w.horder,
+                                                     w.hhist);
   uint64_t *kin = w.hkey_a, *kout = w.hkey_b;
   int32_t *vin = w.horder, *vout = w.hidx;
-  hipError_t e;
   for (int pass = 0; pass < passes; ++pass) {
-    k_rs_hist<kDigKey><<<ntiles, kSortThreads, 0, st>>>(kin, vin, nullptr, w.seg_off, K, n, 8 * pass, w.hhist, ntiles);
-    if ((e = scan_excl(w.hhist, w.hhist, 256 * ntiles, w.hscan, nullptr, st)) != hipSuccess) return e;
-    k_rs_scatter<kDigKey><<<ntiles, kSortThreads, 0, st>>>(kin, vin, nullptr, w.seg_off, K, kout, vout, n, 8 * pass,
-                                                           w.hhist, ntiles);
+    launch_pass<kDigKey>(kin, vin, w, kout, vout, n, 8 * pass, sc, pass, st);
     uint64_t* tk = kin; kin = kout; kout = tk;
     int32_t* tv = vin; vin = vout; vout = tv;
   }

@@ -8,10 +8,15 @@ namespace bh {
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
 constexpr int kScanTile = kScanThreads * kScanItems;
-// radix sort: 256 threads x 16 keys per tile, 8-bit digits
+// radix sort: 8-bit digits, tiles of 256 threads x sort_items keys (a pass over
+// few tiles is bound by one tile's latency: smaller ones spread it over more CUs)
 constexpr int kSortThreads = 256;
-constexpr int kSortItems = 16;
-constexpr int kSortTile = kSortThreads * kSortItems;
+constexpr int kSortPasses = 11;  // 8 key digits and up to 3 cluster digits
+inline int sort_items(int64_t n) { return n <= (1 << 18) ? 4 : n <= (1 << 21) ? 8 : 16; }
+inline int64_t sort_tiles(int64_t n) {
+  const int64_t tile = (int64_t)kSortThreads * sort_items(n);
+  return (n + tile - 1) / tile;
+}
 constexpr int kBboxBlocks = 1024;
 
 // Mass and first moments (sum of m x) of a node, FP64: what a parent's moment
@@ -76,7 +81,9 @@ struct BuildWs {
   int n_bbox_blocks;
   uint64_t *key_a, *key_b;  // [n]
   int32_t *idx_a, *idx_b;   // [n]; idx_a ends as perm (Morton position -> caller index)
-  int32_t* hist;            // [256 * ntiles]
+  int32_t* hist;            // [kSortPasses][256] digit counts of the sort's passes
+  int32_t* ticket;          // [kSortPasses] tiles started
+  uint32_t* tiles;          // [2][sort_tiles][256] words of the look-back
   int32_t* scan_tiles;      // scan scratch
   void* ps;                 // [n] float4 or double4 (x, y, z, m) in Morton order
   int32_t *flag, *uid;      // [n]
@@ -98,8 +105,9 @@ struct BuildWs {
   int32_t* horder;          // [n] Morton positions in the Hilbert walk order (filled on demand)
   uint64_t *hkey_a, *hkey_b;  // [n] sort buffers of the Hilbert order (its own: it may run beside the build)
   int32_t* hidx;            // [n]
-  int32_t* hhist;           // [256 * ntiles]
-  int32_t* hscan;           // scan scratch
+  int32_t* hhist;           // the same as hist, ticket and tiles for its sort
+  int32_t* hticket;
+  uint32_t* htiles;
   QuadRec* qrec;            // [2n + 1] second moments of every node (walks of order 2; filled on demand)
 };
 

@@ -146,6 +146,7 @@ struct NbrArgs {
   int n_seg;
   int n;
   double r2;                   // r^2
+  float r2f;                   // FP32 bound above r^2 for the filter of FP32 trees (+inf: let all pass)
   double inv_h;                // 1/h, h = r/2
   double sig;                  // 1/(pi h^3), the spline's normalisation
   int32_t* count;              // [n] neighbours, caller order
@@ -159,40 +160,38 @@ struct NbrArgs {
 struct NbrTarget {
   double xi, yi, zi;
   double wsum;         // m_i + sum over neighbours of m_j w(q_j); the density is sig * wsum
-  int i, skip, idx0;
+  int i, skip;
   int32_t count;
   uint64_t h;
   int64_t* list;
 };
 
 // w(q) = W(|d|, h) / sig of the M4 cubic spline in three dimensions, from
-// d^2 >= 0, in its truncated-power form: w = (2 - q)_+^3 / 4 - (1 - q)_+^3
-// (equal to 1 - 3/2 q^2 + 3/4 q^3 for q < 1, (2 - q)^3 / 4 for 1 <= q < 2 and
-// 0 beyond, q = |d|/h), which needs no branch or select.  |d| = sqrt(d^2) by
-// Goldschmidt's iteration from the hardware reciprocal square root (one
-// refinement of the root and of the half reciprocal, then a residual
-// correction: within an ulp or two of the rounded root, far inside the
-// density's tolerance).  2^-1000 is added to d^2, so that the iteration never
-// meets 0 * inf: the sum is d^2 itself for d^2 > 2^-947, and below that q is
-// ~1e-142 or less, where w = 1 to the last bit whatever the root.
+// 0 <= d^2 < r^2 (so q = |d|/h < 2), in its truncated-power form: w =
+// (2 - q)^3 / 4 - (1 - q)_+^3 (equal to 1 - 3/2 q^2 + 3/4 q^3 for q < 1 and
+// (2 - q)^3 / 4 beyond), which needs no branch or select.  |d| = sqrt(d^2) from
+// the hardware reciprocal square root y by one third-order step, x y (1 - e)^-1/2
+// with e = 1 - x y^2 (within an ulp or two of the rounded root, far inside the
+// density's tolerance).  2^-1000 is added to d^2, so that the step never meets
+// 0 * inf: the sum is d^2 itself for d^2 > 2^-947, and below that q is ~1e-142
+// or less, where w = 1 to the last bit whatever the root.
 __device__ __forceinline__ double sph_w2(double d2, double inv_h) {
-  const double d2g = d2 + 0x1p-1000;
-  const double y = __builtin_amdgcn_rsq(d2g);
-  double g = d2g * y, hh = 0.5 * y;
-  const double e = fma(-g, hh, 0.5);
-  g = fma(g, e, g);
-  hh = fma(hh, e, hh);
-  g = fma(fma(-g, g, d2g), hh, g);
-  const double q = g * inv_h;
-  const double u = fmax(2.0 - q, 0.0), b = fmax(1.0 - q, 0.0);
+  const double x = d2 + 0x1p-1000;
+  const double y = __builtin_amdgcn_rsq(x);
+  const double g = x * y;
+  const double e = fma(-g, y, 1.0);
+  const double q = fma(g * e, fma(0.375, e, 0.5), g) * inv_h;
+  const double u = 2.0 - q, b = fmax(1.0 - q, 0.0);
   return fma(0.25, (u * u) * u, -((b * b) * b));
 }
 
+// idx0: caller index of the cluster's first particle (wave-uniform: the lanes
+// that get here are of the cluster being walked)
 template <bool kLists>
-__device__ __forceinline__ void nbr_pair(const NbrArgs& a, NbrTarget& T, int caller, double m, double d2) {
+__device__ __forceinline__ void nbr_pair(const NbrArgs& a, NbrTarget& T, int idx0, int caller, double m, double d2) {
   // (j, the caller index relative to the cluster, is in [0, n) with n < 2^30,
   // so j << 1 is exact in 32 bits and leaves the hash's high word alone)
-  const uint32_t j = (uint32_t)(caller - T.idx0);
+  const uint32_t j = (uint32_t)(caller - idx0);
   if constexpr (kLists) {
     if (T.count < a.maxlen) T.list[T.count] = (int64_t)j;
   }
@@ -203,42 +202,63 @@ __device__ __forceinline__ void nbr_pair(const NbrArgs& a, NbrTarget& T, int cal
 
 // The particles [first, first + count) of a group, in Morton (depth-first)
 // order, against the lanes `in` (active, and within reach of the group).
-// Their positions, masses and caller indices are read with scalar loads a few
-// at a time, all loads of a batch in flight together (the last particle is
-// re-read to fill a batch, never one past it).
+//
+// Most particles of a group are within r of no lane (about nine in ten on
+// clumpy 4M at r = 2e-3), so what counts is the test.  Four particles (two in
+// FP64) and their caller indices are read at once, one scalar load each (the
+// last batch reads on into what follows in the workspace: its surplus is never
+// used), tested for the whole wave, and passed over with one branch if no lane
+// is near any of them.  The test of FP32 trees is a filter in FP32, 7
+// instructions instead of 10: its squared distance is within 2^-21 of the exact
+// one (three rounded differences, squared and summed), so a bound 2^-20 above
+// r^2 lets every neighbour pass; what passes takes the exact test in FP64.
 template <bool kF64, bool kLists, bool kOff32>
-__device__ __forceinline__ void nbr_group(const NbrArgs& a, NbrTarget& T, bool in, int first, int count) {
-  typedef float v4f_t __attribute__((ext_vector_type(4)));
-  typedef double v4d_t __attribute__((ext_vector_type(4)));
-  using V4 = typename std::conditional<kF64, v4d_t, v4f_t>::type;
-  constexpr int kBatch = kF64 ? 2 : 4;   // 64 bytes of particles per batch
+__device__ __forceinline__ void nbr_group(const NbrArgs& a, NbrTarget& T, int idx0, bool in, int first, int count) {
+  typedef float v16f_t __attribute__((ext_vector_type(16)));
+  typedef double v8d_t __attribute__((ext_vector_type(8)));
+  typedef int v4i_t __attribute__((ext_vector_type(4)));
+  typedef int v2i_t __attribute__((ext_vector_type(2)));
+  using V = typename std::conditional<kF64, v8d_t, v16f_t>::type;
+  using VI = typename std::conditional<kF64, v2i_t, v4i_t>::type;
+  using R = typename std::conditional<kF64, double, float>::type;
+  typedef V __attribute__((aligned(16))) VA;   // 64 bytes of particles
+  typedef VI __attribute__((aligned(4))) VIA;
+  constexpr int kBatch = kF64 ? 2 : 4;
   const int end = first + count;
+  const R xi = (R)T.xi, yi = (R)T.yi, zi = (R)T.zi;  // (exact: FP32 trees hold FP32 positions)
+  const R bound = in ? (kF64 ? (R)a.r2 : (R)a.r2f) : (R)-1;
+  const double exact = in ? a.r2 : -1.0;
   for (int k0 = first; k0 < end; k0 += kBatch) {
-    V4 q[kBatch];
-    int caller[kBatch];
-#pragma unroll
-    for (int j = 0; j < kBatch; ++j) {
-      const uint32_t k = (uint32_t)min(k0 + j, end - 1);
-      if constexpr (kOff32) {
-        // (32-bit byte offsets: the loads take them in a scalar register)
-        q[j] = *(const BH_CONST V4*)((const BH_CONST char*)(uintptr_t)a.ps + k * (uint32_t)sizeof(V4));
-        caller[j] = *(const BH_CONST int32_t*)((const BH_CONST char*)(uintptr_t)a.perm + k * 4u);
-      } else {
-        q[j] = *((const BH_CONST V4*)(uintptr_t)a.ps + k);
-        caller[j] = *((const BH_CONST int32_t*)(uintptr_t)a.perm + k);
-      }
+    V q;
+    VI caller;
+    if constexpr (kOff32) {
+      // (32-bit byte offsets: the loads take them in a scalar register)
+      const uint32_t k = (uint32_t)k0;
+      q = *(const BH_CONST VA*)((const BH_CONST char*)(uintptr_t)a.ps + k * (uint32_t)(4 * sizeof(R)));
+      caller = *(const BH_CONST VIA*)((const BH_CONST char*)(uintptr_t)a.perm + k * 4u);
+    } else {
+      q = *(const BH_CONST VA*)((const BH_CONST char*)(uintptr_t)a.ps + (uint64_t)(uint32_t)k0 * (4 * sizeof(R)));
+      caller = *(const BH_CONST VIA*)((const BH_CONST char*)(uintptr_t)a.perm + (uint64_t)(uint32_t)k0 * 4u);
     }
-    // (every value of the batch taken here, in scalar registers: one wait for
-    // the whole batch, instead of loads sunk into the per-particle branches)
-#pragma unroll
-    for (int j = 0; j < kBatch; ++j) asm volatile("" ::"s"(q[j].x), "s"(q[j].y), "s"(q[j].z), "s"(q[j].w), "s"(caller[j]));
+    uint64_t m[kBatch], any = 0;
 #pragma unroll
     for (int j = 0; j < kBatch; ++j) {
-      if (k0 + j < end) {
-        const double dx = (double)q[j].x - T.xi, dy = (double)q[j].y - T.yi, dz = (double)q[j].z - T.zi;
-        const double d2 = fma(dz, dz, fma(dy, dy, dx * dx));
-        if (in && d2 < a.r2 && k0 + j != T.i) nbr_pair<kLists>(a, T, caller[j], (double)q[j].w, d2);
+      if constexpr (kF64) {
+        const double dx = q[4 * j] - xi, dy = q[4 * j + 1] - yi, dz = q[4 * j + 2] - zi;
+        m[j] = __builtin_amdgcn_fcmp(fma(dz, dz, fma(dy, dy, dx * dx)), bound, 4);  // ordered <
+      } else {
+        const float dx = q[4 * j] - xi, dy = q[4 * j + 1] - yi, dz = q[4 * j + 2] - zi;
+        m[j] = __builtin_amdgcn_fcmpf(fmaf(dz, dz, fmaf(dy, dy, dx * dx)), bound, 4);
       }
+      any |= m[j];
+    }
+    if (any == 0ull) continue;
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      if (m[j] == 0ull || k0 + j >= end) continue;
+      const double dx = (double)q[4 * j] - T.xi, dy = (double)q[4 * j + 1] - T.yi, dz = (double)q[4 * j + 2] - T.zi;
+      const double d2 = fma(dz, dz, fma(dy, dy, dx * dx));
+      if (d2 < exact && k0 + j != T.i) nbr_pair<kLists>(a, T, idx0, caller[j], (double)q[4 * j + 3], d2);
     }
   }
 }
@@ -250,7 +270,8 @@ __device__ __forceinline__ void nbr_group(const NbrArgs& a, NbrTarget& T, bool i
 // when a lane can reach it, its particles are tested directly, and the walk
 // goes on after its subtree.
 template <bool kF64, bool kLists, bool kOff32, typename Fetch>
-__device__ __forceinline__ void nbr_step(const NbrArgs& a, NbrTarget& T, int& c, const NbrRec& rec, Fetch fetch) {
+__device__ __forceinline__ void nbr_step(const NbrArgs& a, NbrTarget& T, int idx0, int& c, const NbrRec& rec,
+                                         Fetch fetch) {
   const int nnext = uniform(rec.next), first = uniform(rec.first), tag = uniform(rec.tag);
   // (the mass goes with the step's first batch of scalar loads: a load left to
   // the leaf's branch would cost the step a second round trip)
@@ -272,9 +293,9 @@ __device__ __forceinline__ void nbr_step(const NbrArgs& a, NbrTarget& T, int& c,
   } else if (m_in) {
     // (a group is not descended: every lane active here is active after it)
     if (tag >= 0) {
-      if (act && in && first != T.i) nbr_pair<kLists>(a, T, tag, rec.m, d2);
+      if (act && in && first != T.i) nbr_pair<kLists>(a, T, idx0, tag, rec.m, d2);
     } else {
-      nbr_group<kF64, kLists, kOff32>(a, T, act && in, first, uniform(rec.count));
+      nbr_group<kF64, kLists, kOff32>(a, T, idx0, act && in, first, uniform(rec.count));
     }
   }
   c = cn;
@@ -284,18 +305,18 @@ __device__ __forceinline__ void nbr_step(const NbrArgs& a, NbrTarget& T, int& c,
 // cap = 2n and every next pointer is at most cap, so the look-ahead read stays
 // inside it.
 template <bool kF64, bool kLists, bool kOff32>
-__device__ void nbr_subtree(const NbrArgs& a, NbrTarget& T, int c, int end) {
+__device__ void nbr_subtree(const NbrArgs& a, NbrTarget& T, int idx0, int c, int end) {
   NbrRec cur = nbr_load<kOff32>(a.wn, c);
   while (c < end) {
     NbrRec nx;
-    nbr_step<kF64, kLists, kOff32>(a, T, c, cur, [&](int cn) { nx = nbr_load<kOff32>(a.wn, cn); });
+    nbr_step<kF64, kLists, kOff32>(a, T, idx0, c, cur, [&](int cn) { nx = nbr_load<kOff32>(a.wn, cn); });
     cur = nx;
   }
 }
 
 // kLists: the caller asked for neighbour lists (a.lists non-null).
 template <bool kF64, bool kLists>
-__global__ __launch_bounds__(64) void k_nbr(NbrArgs a) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void k_nbr(NbrArgs a) {
   using T4 = typename std::conditional<kF64, double4, float4>::type;
   using R = typename std::conditional<kF64, double, float>::type;
   const int group = remap_block(blockIdx.x, gridDim.x, a.xcd_chunk);
@@ -318,7 +339,6 @@ __global__ __launch_bounds__(64) void k_nbr(NbrArgs a) {
   T.h = kFnvOffset;
   T.list = (kLists && valid) ? a.lists + (int64_t)a.perm[T.i] * a.maxlen : nullptr;
   const int kc = (valid && a.scid) ? min(max(a.scid[T.i], 0), a.n_seg - 1) : 0;
-  T.idx0 = valid ? (int)a.seg_off[kc] : 0;
   int klo = valid ? kc : 0x7fffffff, khi = valid ? kc : -1;
   for (int o = 32; o > 0; o >>= 1) {
     klo = min(klo, __shfl_xor(klo, o, 64));
@@ -333,10 +353,11 @@ __global__ __launch_bounds__(64) void k_nbr(NbrArgs a) {
     const int r1 = min(max(uniform(a.croot[k + 1]), r0), cap);
     T.skip = (valid && kc == k) ? r0 : 0x7fffffff;
     if (r0 >= r1) continue;
+    const int idx0 = uniform((int)a.seg_off[k]);
     if (off32)
-      nbr_subtree<kF64, kLists, true>(a, T, r0, r1);
+      nbr_subtree<kF64, kLists, true>(a, T, idx0, r0, r1);
     else
-      nbr_subtree<kF64, kLists, false>(a, T, r0, r1);
+      nbr_subtree<kF64, kLists, false>(a, T, idx0, r0, r1);
   }
   if (!valid) return;
   const int o = a.perm[T.i];
@@ -368,6 +389,9 @@ hipError_t launch_neighbours(bool f64, const Node* nodes, const Counts* counts, 
   a.n_seg = n_seg;
   a.n = n;
   a.r2 = radius * radius;
+  // the filter's bound: 2^-20 above r^2, where FP32 squares neither overflow nor
+  // lose anything that counts against r^2; outside that range everything passes
+  a.r2f = radius > 1e-15 && radius < 1e15 ? (float)(a.r2 * (1.0 + 0x1p-20)) : __builtin_huge_valf();
   const double h = 0.5 * radius;
   a.inv_h = 1.0 / h;
   a.sig = 1.0 / (3.141592653589793 * h * h * h);

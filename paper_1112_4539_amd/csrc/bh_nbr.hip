@@ -14,8 +14,8 @@
 // the centre of mass, so a target whose squared distance to the centre of
 // mass is at least R2 has no neighbour in the cell (the factor keeps the
 // bound safe under rounding).  A leaf of one particle carries r^2, the exact
-// test, so cells and leaves take the same test.  A cell of at most kNbrGroup
-// particles is a group: when a lane can reach it, the wave tests its
+// test, so cells and leaves take the same test.  A cell of at most
+// nbr_group_max particles is a group: when a lane can reach it, the wave tests its
 // particles directly, read in Morton order from the particle array (which is
 // the depth-first order of its leaves), and moves on past its subtree; a leaf
 // of several particles (coincident Morton keys) is a group that every active
@@ -37,7 +37,7 @@ namespace {
 //   first      : Morton position of the first particle
 //   count      : particles in the subtree
 //   tag        : -1 cell, >= 0 the caller index of a one-particle leaf's
-//                particle, -2 a group: a cell of at most kNbrGroup particles
+//                particle, -2 a group: a cell of at most nbr_group_max particles
 //                or a leaf of several, whose particles are tested directly
 struct alignas(64) NbrRec {
   double cx, cy, cz, R2, m;
@@ -48,10 +48,12 @@ static_assert(sizeof(NbrRec) == sizeof(WalkNode), "the neighbour walk copy share
 constexpr int32_t kTagCell = -1, kTagGroup = -2;
 // Cells of at most this many particles are walked as groups: their particles
 // are tested directly, four (FP32) or two (FP64) per round trip, instead of
-// one dependent record load per node of their subtree.  On the clumpy 4M
-// field at r = 2e-3 the search takes 8.7 ms with no groups, 6.8 ms with
-// groups of 8, 6.0 ms with 24-32 and 6.3 ms with 64.
-constexpr int kNbrGroup = 32;
+// one dependent record load per node of their subtree.  Larger groups test more
+// particles in vain and save round trips; the FP64 test is the dearer one.  On
+// the clumpy 4M field at r = 2e-3 the search takes, for groups of 24, 32, 48, 64
+// and 96, 4.93, 4.79, 4.65, 4.48 and 4.42 ms (FP32) and 5.29, 5.21, 5.19, 5.32 and
+// 5.60 ms (FP64); at r = 1e-3 and for other fields 64 and 96 are the same.
+constexpr int nbr_group_max(bool f64) { return f64 ? 48 : 64; }
 
 template <bool kOff32>
 __device__ __forceinline__ NbrRec nbr_load(const NbrRec* base, int c) {
@@ -376,8 +378,9 @@ hipError_t launch_neighbours(bool f64, const Node* nodes, const Counts* counts, 
   if (n <= 0) return hipSuccess;
   const int cap = 2 * n;
   NbrRec* rec = reinterpret_cast<NbrRec*>(copy);
-  k_nbr_copy<<<(cap + 255) / 256, 256, 0, st>>>(nodes, counts, perm, cap, radius, kNbrGroup, rec);
-  k_nbr_roots<<<(n_seg + 63) / 64, 64, 0, st>>>(nodes, counts, perm, croot, n_seg, cap, radius, kNbrGroup, rec);
+  const int group_max = nbr_group_max(f64);
+  k_nbr_copy<<<(cap + 255) / 256, 256, 0, st>>>(nodes, counts, perm, cap, radius, group_max, rec);
+  k_nbr_roots<<<(n_seg + 63) / 64, 64, 0, st>>>(nodes, counts, perm, croot, n_seg, cap, radius, group_max, rec);
   NbrArgs a{};
   a.wn = rec;
   a.ps = ps;

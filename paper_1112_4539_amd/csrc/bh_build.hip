@@ -702,27 +702,25 @@ __device__ __forceinline__ bool same_cell(uint64_t a, uint64_t b, int level) {
 }
 
 // Key range [f, l] of the cell of level s that separates the adjacent unique
-// keys j (kj) and j + 1 (kj1), by galloping and binary search (keys are sorted,
-// so a range shares a prefix iff its ends do); true if j | j + 1 is the cell's
-// first child boundary.  key(m): unique key m; mine(m): key m is of j's cluster.
-template <typename Key, typename Mine>
-__device__ __forceinline__ bool cell_range(int j, int U, int s, uint64_t kj, uint64_t kj1, Key&& key, Mine&& mine,
+// keys j (kj) and j + 1 (kj1) of a cluster with unique keys [ulo, uhi), by
+// galloping and binary search (keys are sorted, so a range shares a prefix iff
+// its ends do); true if j | j + 1 is the cell's first child boundary.  key(m):
+// unique key m.
+template <typename Key>
+__device__ __forceinline__ bool cell_range(int j, int ulo, int uhi, int s, uint64_t kj, uint64_t kj1, Key&& key,
                                            int& f_out, int& l_out) {
-  auto in_cell = [&](int m, uint64_t ref) { return mine(m) && same_cell(key(m), ref, s); };
   // first key of the cell: smallest f <= j with same_cell(key(f), kj, s)
   int lo = j, step = 1;
   while (true) {
     int cand = j - step;
-    if (cand < 0 || !in_cell(cand, kj)) break;
+    if (cand < ulo || !same_cell(key(cand), kj, s)) break;
     lo = cand;
     step <<= 1;
   }
-  int hi_bad = j - step;  // < 0 or outside the cell
-  int a = hi_bad, b = lo;  // invariant: a outside (or -1), b inside
-  if (a < -1) a = -1;
+  int a = max(j - step, ulo - 1), b = lo;  // invariant: a outside (or ulo - 1), b inside
   while (b - a > 1) {
     int m = a + (b - a) / 2;
-    if (in_cell(m, kj)) b = m; else a = m;
+    if (same_cell(key(m), kj, s)) b = m; else a = m;
   }
   const int f = b;
   // last key of the cell: largest l >= j+1 with same_cell(key(l), kj1, s)
@@ -730,15 +728,14 @@ __device__ __forceinline__ bool cell_range(int j, int U, int s, uint64_t kj, uin
   step = 1;
   while (true) {
     int cand = j + 1 + step;
-    if (cand >= U || !in_cell(cand, kj1)) break;
+    if (cand >= uhi || !same_cell(key(cand), kj1, s)) break;
     up = cand;
     step <<= 1;
   }
-  int c = up, d = j + 1 + step;  // c inside, d outside (or U)
-  if (d > U) d = U;
+  int c = up, d = min(j + 1 + step, uhi);  // c inside, d outside (or uhi)
   while (d - c > 1) {
     int m = c + (d - c) / 2;
-    if (in_cell(m, kj1)) c = m; else d = m;
+    if (same_cell(key(m), kj1, s)) c = m; else d = m;
   }
   f_out = f;
   l_out = c;
@@ -759,6 +756,7 @@ __device__ __forceinline__ bool cell_range(int j, int U, int s, uint64_t kj, uin
 // tile, and only those that run past it read the key array in memory.
 constexpr int kPairHalo = 512;
 __global__ __launch_bounds__(256) void k_pairs(const uint64_t* __restrict__ ukey, const int32_t* __restrict__ ucid,
+                                               const int32_t* __restrict__ croot,
                                                const Counts* __restrict__ cnt,
                                                int32_t* __restrict__ split, int32_t* __restrict__ rep,
                                                int32_t* __restrict__ pf, int32_t* __restrict__ pl, int nmax) {
@@ -775,8 +773,16 @@ __global__ __launch_bounds__(256) void k_pairs(const uint64_t* __restrict__ ukey
     rep[j] = 0;
     return;
   }
-  const int cj = ucid ? ucid[j] : 0;
-  if (ucid && ucid[j + 1] != cj) {
+  // (unique keys [ulo, uhi) are the cluster's: croot holds every cluster's first
+  // one at this point; a read of each key's cluster id in the search made the
+  // kernel 478 us for a forest of 7.5M particles, it takes 307)
+  int ulo = 0, uhi = U;
+  if (ucid) {
+    const int cj = ucid[j];
+    ulo = croot[cj];
+    uhi = croot[cj + 1];
+  }
+  if (j + 1 >= uhi) {
     split[j] = -1;
     rep[j] = 0;
     return;
@@ -786,7 +792,7 @@ __global__ __launch_bounds__(256) void k_pairs(const uint64_t* __restrict__ ukey
   split[j] = s;
   int f, l;
   const bool is_rep = cell_range(
-      j, U, s, kj, kj1, key, [&](int m) { return !ucid || ucid[m] == cj; }, f, l);
+      j, ulo, uhi, s, kj, kj1, key, f, l);
   rep[j] = is_rep ? 1 : 0;
   pf[j] = f;
   pl[j] = l;
@@ -1343,7 +1349,7 @@ static hipError_t build_impl(const T* pos, const T* mass, int n, const BuildWs& 
                                                w.counts, w.nstart, w.lmask);
   k_croot_first<<<nblk(K + 1, 256), 256, 0, st>>>(w.seg_off, K, n, w.uid, w.counts, w.croot);
   // internal nodes
-  k_pairs<<<nblk(n, 256), 256, 0, st>>>(w.ukey, ucid, w.counts, w.split, w.flag, w.pf, w.pl, n);
+  k_pairs<<<nblk(n, 256), 256, 0, st>>>(w.ukey, ucid, w.croot, w.counts, w.split, w.flag, w.pf, w.pl, n);
   if ((e = scan_excl(w.flag, w.uid, n, w.scan_tiles, nullptr, st)) != hipSuccess) return e;
   k_internal_write<<<nblk(n, 256), 256, 0, st>>>(w.flag, w.uid, w.split, w.pf, w.pl, w.counts, w.ilevel, w.ifirst,
                                                  w.ilast, w.nstart, w.lmask, n);
@@ -1730,7 +1736,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(const T* __restri
     const int lev = split_level(kj, kj1);
     s.split[j] = (int8_t)lev;
     if (cell_range(
-            j, U, lev, kj, kj1, [&](int m) { return s.topo.ukey[m]; }, [](int) { return true; }, nf[k], nl[k])) {
+            j, 0, U, lev, kj, kj1, [&](int m) { return s.topo.ukey[m]; }, nf[k], nl[k])) {
       ns[k] = lev;
       atomicAdd(&s.topo.nstart[nf[k]], 1);
       atomicOr(&s.topo.lmask[nf[k]], 1u << lev);

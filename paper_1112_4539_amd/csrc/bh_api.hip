@@ -28,7 +28,9 @@ struct bh_tree {
   mutable bool rank_ready = false;
   int32_t* queue = nullptr; // group counter of the persistent walk
   int waves_per_block = 1;
-  int xcd_chunk = -1;  // -1: 1024 for FP32 trees (about the one-wave workgroups an XCD holds), 0 for FP64
+  int xcd_chunk = -1;  // -1: 1024 for FP32 trees (about the one-wave workgroups an XCD holds), 64 for FP64
+                       // (Plummer 1M, theta 0.5: 4054 us without runs, 3823, 3938 and 3951 with runs of 64, 256
+                       // and 1024; clumpy 1M, theta 0.35: 7071, 6578, 6553, 6532; order 2: within 3 %)
   int target_order = 2;
   mutable bool horder_ready = false;  // w.horder holds the Hilbert order of the current build
   int order = 1;                      // cell terms: 1 monopole, 2 with the quadrupole correction
@@ -348,7 +350,7 @@ int run_walk(const bh_tree* t, double theta, const float* theta_group, double ep
   a.lists = lists;
   a.maxlen = maxlen;
   a.group_steps = group_steps;
-  a.xcd_chunk = t->xcd_chunk >= 0 ? t->xcd_chunk : (t->prec == BH_FP64 ? 0 : 1024);
+  a.xcd_chunk = t->xcd_chunk >= 0 ? t->xcd_chunk : (t->prec == BH_FP64 ? 64 : 1024);
   a.lds_share64 = t->lds_share64;
   a.waves_per_block = t->waves_per_block;
   a.persistent = t->persistent;
@@ -636,7 +638,9 @@ int bh_neighbours(const bh_tree* t, double radius, int32_t* count, uint64_t* has
     if (e != hipSuccess) return hip_fail(e, "launching the target order");
   }
   const int32_t* order = walk_order_of(t);
-  const int chunk = t->xcd_chunk >= 0 ? t->xcd_chunk : (t->prec == BH_FP64 ? 0 : 1024);
+  // (FP64, clumpy 4M, r = 2e-3: 5062 us without runs, 4877 with runs of 1024; clumpy 1M 1478 and 1322;
+  // Plummer 300,000 680 and 606)
+  const int chunk = t->xcd_chunk >= 0 ? t->xcd_chunk : 1024;
   hipError_t e = bh::launch_neighbours(t->prec == BH_FP64, t->w.nodes, t->w.counts, t->w.wnodes, t->w.ps, t->w.idx_a,
                                        order, t->n_seg > 1 ? t->w.scid : nullptr, t->w.croot, t->w.seg_off,
                                        (int)t->n_seg, (int)t->n, radius, count, hash, lists, lists ? maxlen : 0, rho,

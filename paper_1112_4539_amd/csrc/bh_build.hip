@@ -1513,6 +1513,7 @@ static hipError_t hilbert_impl(int n, const BuildWs& w, hipStream_t st) {
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / kWave;
 constexpr int kSmallItems = kSmallBuild / kSmallThreads;
+constexpr int kSmallRun = 16;
 
 struct SmallLds {
   union {
@@ -1537,7 +1538,7 @@ struct SmallLds {
   int32_t scan[kSmallWaves];
   double red[6][kSmallWaves];
   Cube cube;
-  int32_t bad;
+  int32_t bad, long_run;
 };
 static_assert(sizeof(SmallLds) <= 160 * 1024, "the small build's arrays must fit the LDS");
 
@@ -1643,7 +1644,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(const T* __restri
       }
       if (!isfinite((double)mass[i])) bad = true;
     }
-    if (t == 0) s.bad = 0;
+    if (t == 0) s.bad = s.long_run = 0;
 #pragma unroll
     for (int q = 0; q < 6; ++q) {
       for (int o = 32; o > 0; o >>= 1) {
@@ -1684,7 +1685,38 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(const T* __restri
     s.sort.idx[0][i] = i;
   }
   __syncthreads();
-  for (int pass = 0; pass < 8; ++pass) small_sort_pass(s, n, 8 * pass, pass & 1);
+  // By the upper 32 key bits first, four passes instead of eight: few particles
+  // of a small set share them (a cell ten levels down), and where they do, the
+  // first of them puts them into order by the whole key.  Longer runs of one cell
+  // take the other digits as well; a stable sort from the lowest digit up may
+  // start from any order that keeps equal keys by index.
+  for (int pass = 0; pass < 4; ++pass) small_sort_pass(s, n, 31 + 8 * pass, pass & 1);
+  for (int j = t; j < n; j += kSmallThreads) {
+    const uint64_t hi = s.sort.key[0][j] >> 31;
+    if (j > 0 && s.sort.key[0][j - 1] >> 31 == hi) continue;
+    int e = j + 1;
+    while (e < n && e - j <= kSmallRun && s.sort.key[0][e] >> 31 == hi) ++e;
+    if (e - j > kSmallRun) {
+      s.long_run = 1;
+      continue;
+    }
+    for (int i = j + 1; i < e; ++i) {
+      const uint64_t key = s.sort.key[0][i];
+      const int32_t id = s.sort.idx[0][i];
+      int q = i;
+      for (; q > j && s.sort.key[0][q - 1] > key; --q) {
+        s.sort.key[0][q] = s.sort.key[0][q - 1];
+        s.sort.idx[0][q] = s.sort.idx[0][q - 1];
+      }
+      s.sort.key[0][q] = key;
+      s.sort.idx[0][q] = id;
+    }
+  }
+  __syncthreads();
+  if (s.long_run) {
+    for (int pass = 0; pass < 4; ++pass) small_sort_pass(s, n, 8 * pass, pass & 1);
+    for (int pass = 0; pass < 4; ++pass) small_sort_pass(s, n, 31 + 8 * pass, pass & 1);
+  }
   for (int k = t; k < n; k += kSmallThreads) {
     const int j = s.sort.idx[0][k];
     a.perm[k] = j;

@@ -105,19 +105,15 @@ size_t layout(int64_t n, int64_t K, int prec, char* base, bh::BuildWs* w, int32_
   t.idx_a = reinterpret_cast<int32_t*>(take(4 * N));
   t.idx_b = reinterpret_cast<int32_t*>(take(4 * N));
   t.hist = reinterpret_cast<int32_t*>(take(4 * 256 * bh::kSortPasses));
-  t.ticket = reinterpret_cast<int32_t*>(take(4 * bh::kSortPasses));
+  t.ticket = reinterpret_cast<int32_t*>(take(4 * (bh::kSortPasses + 1)));
   t.tiles = reinterpret_cast<uint32_t*>(take(4 * words));
   t.scan_tiles = reinterpret_cast<int32_t*>(take(4 * scan_tiles));
   t.ps = take(ps);
   t.flag = reinterpret_cast<int32_t*>(take(4 * N));
-  t.uid = reinterpret_cast<int32_t*>(take(4 * N));
   t.ustart = reinterpret_cast<int32_t*>(take(4 * (N + 1)));
   t.split = reinterpret_cast<int32_t*>(take(4 * N));
   t.pf = reinterpret_cast<int32_t*>(take(4 * N));
   t.pl = reinterpret_cast<int32_t*>(take(4 * N));
-  t.ilevel = reinterpret_cast<int32_t*>(take(4 * N));
-  t.ifirst = reinterpret_cast<int32_t*>(take(4 * N));
-  t.ilast = reinterpret_cast<int32_t*>(take(4 * N));
   t.nstart = reinterpret_cast<int32_t*>(take(4 * (N + 1)));
   t.nexcl = reinterpret_cast<int32_t*>(take(4 * (N + 1)));
   t.lmask = reinterpret_cast<uint32_t*>(take(4 * (N + 1)));
@@ -139,7 +135,7 @@ size_t layout(int64_t n, int64_t K, int prec, char* base, bh::BuildWs* w, int32_
   t.hkey_b = reinterpret_cast<uint64_t*>(take(8 * N));
   t.hidx = reinterpret_cast<int32_t*>(take(4 * N));
   t.hhist = reinterpret_cast<int32_t*>(take(4 * 256 * bh::kSortPasses));
-  t.hticket = reinterpret_cast<int32_t*>(take(4 * bh::kSortPasses));
+  t.hticket = reinterpret_cast<int32_t*>(take(4 * (bh::kSortPasses + 1)));
   t.htiles = reinterpret_cast<uint32_t*>(take(4 * words));
   t.qrec = reinterpret_cast<bh::QuadRec*>(take(sizeof(bh::QuadRec) * (nodes + 1)));
   int32_t* r = reinterpret_cast<int32_t*>(take(4 * N));

@@ -630,52 +630,106 @@ __global__ __launch_bounds__(256) void k_gather(const T* __restrict__ pos, const
 }
 
 // ---------------------------------------------------------------- unique keys
-// A leaf per distinct (cluster, key).
-__global__ __launch_bounds__(256) void k_unique_flags(const uint64_t* __restrict__ keys,
-                                                      const int32_t* __restrict__ scid, int n,
-                                                      int32_t* __restrict__ flag) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  flag[i] = (i == 0 || keys[i] != keys[i - 1] || (scid && scid[i] != scid[i - 1])) ? 1 : 0;
-}
+// A leaf per distinct (cluster, key): their keys, first positions and clusters,
+// compacted in one pass with the look-back of the sort (one word per tile, 64
+// tiles at a time); and the first unique key of every cluster (the sort keeps
+// cluster k at Morton positions [off[k], off[k+1])), U for empty trailing ones.
+// It also clears the counters of k_pairs.  (Flags, two scan kernels and the
+// write took 36 us for 1M particles and 80 for 4M; this takes 23 and 52.)
+constexpr int kUniqueItems = 8;
+constexpr int kUniqueTile = kSortThreads * kUniqueItems;
+inline int unique_tiles(int64_t n) { return (int)((n + kUniqueTile - 1) / kUniqueTile); }
 
-__global__ __launch_bounds__(256) void k_unique_write(const uint64_t* __restrict__ keys,
-                                                      const int32_t* __restrict__ scid, int n,
-                                                      const int32_t* __restrict__ flag,
-                                                      const int32_t* __restrict__ uid,
-                                                      uint64_t* __restrict__ ukey, int32_t* __restrict__ ustart,
-                                                      int32_t* __restrict__ ucid, Counts* __restrict__ cnt,
-                                                      int32_t* __restrict__ nstart, uint32_t* __restrict__ lmask) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  // (cleared here for k_internal_write)
-  nstart[i] = 0;
-  lmask[i] = 0;
-  if (i == n - 1) {
-    nstart[n] = 0;
-    lmask[n] = 0;
+__global__ __launch_bounds__(kSortThreads) void k_unique(const uint64_t* __restrict__ keys,
+                                                         const int32_t* __restrict__ scid, int n, int K,
+                                                         uint64_t* __restrict__ ukey, int32_t* __restrict__ ustart,
+                                                         int32_t* __restrict__ ucid, Counts* __restrict__ cnt,
+                                                         int32_t* __restrict__ nstart, uint32_t* __restrict__ lmask,
+                                                         int32_t* __restrict__ croot, uint32_t* tiles,
+                                                         int32_t* __restrict__ ticket, int ntiles) {
+  constexpr int kWaves = kSortThreads / 64;
+  __shared__ int chunk[kUniqueItems * kWaves];  // unique keys of each 64 items, then those before them in the tile
+  __shared__ int tile_s, before_s;
+  const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+  if (t == 0) tile_s = atomicAdd(ticket, 1);
+  __syncthreads();
+  const int tile = tile_s;
+  if (tile >= ntiles) return;
+  const int i0 = tile * kUniqueTile;
+  uint64_t key[kUniqueItems], mask[kUniqueItems];
+#pragma unroll
+  for (int r = 0; r < kUniqueItems; ++r) {
+    const int i = i0 + r * kSortThreads + t;
+    const bool valid = i < n;
+    key[r] = valid ? keys[i] : 0ull;
+    const bool fl = valid && (i == 0 || key[r] != keys[i - 1] || (scid && scid[i] != scid[i - 1]));
+    mask[r] = ballot(fl);
+    if (lane == 0) chunk[r * kWaves + w] = __popcll(mask[r]);
+    if (valid) {
+      nstart[i] = 0;
+      lmask[i] = 0;
+    }
   }
-  if (flag[i]) {
-    ukey[uid[i]] = keys[i];
-    ustart[uid[i]] = i;
-    if (ucid) ucid[uid[i]] = scid[i];
+  __syncthreads();
+  if (w == 0) {
+    // the tile's count, the chunks' offsets, and the tiles before this one
+    const int c = lane < kUniqueItems * kWaves ? chunk[lane] : 0;
+    const int incl = wave_incl_scan(c, lane);
+    if (lane < kUniqueItems * kWaves) chunk[lane] = incl - c;
+    const uint32_t total = (uint32_t)__shfl(incl, 63, 64);
+    if (lane == 0)
+      __hip_atomic_store(tiles + tile, (tile == 0 ? kTileTotal : kTileCount) | total, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t before = 0;
+    for (int p = tile - 1; p >= 0;) {
+      const uint32_t word = p - lane >= 0 ? __hip_atomic_load(tiles + (p - lane), __ATOMIC_RELAXED,
+                                                              __HIP_MEMORY_SCOPE_AGENT)
+                                          : kTileTotal;
+      // the nearest tiles up to the first that knows its total; all of them must have a word
+      const uint64_t totals = ballot((word & kTileTotal) != 0u), empty = ballot(word == 0u);
+      const int last = totals ? __builtin_ctzll(totals) : 63;
+      const uint64_t need = last == 63 ? ~0ull : (2ull << last) - 1ull;
+      if (empty & need) {
+        __builtin_amdgcn_s_sleep(1);
+        continue;
+      }
+      uint32_t v = lane <= last ? word & kTileMask : 0u;
+      for (int o = 32; o > 0; o >>= 1) v += (uint32_t)__shfl_xor((int)v, o, 64);
+      before += v;
+      p = totals ? -1 : p - 64;
+    }
+    if (lane == 0) {
+      if (tile > 0)
+        __hip_atomic_store(tiles + tile, kTileTotal | (before + total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      before_s = (int)before;
+      if (tile == ntiles - 1) {
+        const int U = (int)(before + total);
+        cnt->n_unique = U;
+        ustart[U] = n;
+        nstart[n] = 0;
+        lmask[n] = 0;
+        for (int k = scid ? min(max(scid[n - 1], 0), K - 1) + 1 : 1; k <= K; ++k) croot[k] = U;
+      }
+    }
   }
-  if (i == n - 1) {
-    int U = uid[i] + flag[i];
-    ustart[U] = n;
-    cnt->n_unique = U;
+  __syncthreads();
+  const int before = before_s;
+  const uint64_t lt = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int r = 0; r < kUniqueItems; ++r) {
+    if (!((mask[r] >> lane) & 1ull)) continue;
+    const int i = i0 + r * kSortThreads + t;
+    const int u = before + chunk[r * kWaves + w] + __popcll(mask[r] & lt);
+    ukey[u] = key[r];
+    ustart[u] = i;
+    if (scid) {
+      const int c = min(max(scid[i], 0), K - 1), c1 = i > 0 ? min(max(scid[i - 1], 0), K - 1) : -1;
+      ucid[u] = c;
+      for (int k = c1 + 1; k <= c; ++k) croot[k] = u;
+    } else if (i == 0) {
+      croot[0] = 0;
+    }
   }
-}
-
-// First unique key of every cluster (the sort keeps cluster k at Morton
-// positions [off[k], off[k+1])); U for an empty trailing cluster.
-__global__ __launch_bounds__(256) void k_croot_first(const int64_t* __restrict__ off, int K, int n,
-                                                     const int32_t* __restrict__ uid,
-                                                     const Counts* __restrict__ cnt, int32_t* __restrict__ croot) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k > K) return;
-  const int64_t b = clamp_off(off[k], n);
-  croot[k] = b < n ? uid[b] : cnt->n_unique;
 }
 
 // Preorder id of the cluster's root: the shallowest node starting at its first
@@ -759,7 +813,8 @@ __global__ __launch_bounds__(256) void k_pairs(const uint64_t* __restrict__ ukey
                                                const int32_t* __restrict__ croot,
                                                const Counts* __restrict__ cnt,
                                                int32_t* __restrict__ split, int32_t* __restrict__ rep,
-                                               int32_t* __restrict__ pf, int32_t* __restrict__ pl, int nmax) {
+                                               int32_t* __restrict__ pf, int32_t* __restrict__ pl,
+                                               int32_t* __restrict__ nstart, uint32_t* __restrict__ lmask, int nmax) {
   __shared__ uint64_t tile[256 + 2 * kPairHalo];
   const int U = cnt->n_unique;
   const int j0 = blockIdx.x * blockDim.x;
@@ -794,32 +849,9 @@ __global__ __launch_bounds__(256) void k_pairs(const uint64_t* __restrict__ ukey
   const bool is_rep = cell_range(
       j, ulo, uhi, s, kj, kj1, key, f, l);
   rep[j] = is_rep ? 1 : 0;
+  if (!is_rep) return;
   pf[j] = f;
   pl[j] = l;
-}
-
-__global__ __launch_bounds__(256) void k_internal_write(const int32_t* __restrict__ rep,
-                                                        const int32_t* __restrict__ irank,
-                                                        const int32_t* __restrict__ split,
-                                                        const int32_t* __restrict__ pf, const int32_t* __restrict__ pl,
-                                                        Counts* __restrict__ cnt, int32_t* __restrict__ ilevel,
-                                                        int32_t* __restrict__ ifirst, int32_t* __restrict__ ilast,
-                                                        int32_t* __restrict__ nstart, uint32_t* __restrict__ lmask,
-                                                        int nmax) {
-  int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= nmax) return;
-  const int U = cnt->n_unique;
-  if (j == 0) {
-    int I = (U >= 2) ? irank[U - 2] + rep[U - 2] : 0;
-    cnt->n_internal = I;
-    cnt->n_nodes = U + I;
-  }
-  if (j >= U - 1 || !rep[j]) return;
-  int v = irank[j];
-  int s = split[j], f = pf[j];
-  ilevel[v] = s;
-  ifirst[v] = f;
-  ilast[v] = pl[j];
   atomicAdd(&nstart[f], 1);
   atomicOr(&lmask[f], 1u << s);
 }
@@ -911,12 +943,11 @@ __device__ __forceinline__ Node leaf_node(const Cube* __restrict__ cube, int pre
   return nd;
 }
 
-template <typename T4>
 __global__ __launch_bounds__(256) void k_nodes_internal(const Counts* __restrict__ cnt, const Cube* __restrict__ cubes,
                                                         const int32_t* __restrict__ ucid,
-                                                        const int32_t* __restrict__ ilevel,
-                                                        const int32_t* __restrict__ ifirst,
-                                                        const int32_t* __restrict__ ilast,
+                                                        const int32_t* __restrict__ rep,
+                                                        const int32_t* __restrict__ split,
+                                                        const int32_t* __restrict__ pf, const int32_t* __restrict__ pl,
                                                         const int32_t* __restrict__ nstart,
                                                         const int32_t* __restrict__ nexcl,
                                                         const uint32_t* __restrict__ lmask,
@@ -926,9 +957,10 @@ __global__ __launch_bounds__(256) void k_nodes_internal(const Counts* __restrict
                                                         const int64_t* __restrict__ seg_off,
                                                         const int32_t* __restrict__ croot,
                                                         int32_t* __restrict__ anc, int nmax) {
-  int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= nmax || v >= cnt->n_internal) return;
-  const int s = ilevel[v], f = ifirst[v], l = ilast[v];
+  // (a thread per pair of adjacent unique keys; the pairs that stand for a cell)
+  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+  if (j >= nmax || j >= cnt->n_unique - 1 || !rep[j]) return;
+  const int s = split[j], f = pf[j], l = pl[j];
   const int pre = f + nexcl[f] + __popc(lmask[f] & ((1u << s) - 1u));
   const int cl = ucid ? ucid[f] : 0;
   const Node nd = internal_node(cubes[cl], ukey[f], s, l + nexcl[l] + nstart[l] + 1, ustart[f], ustart[l + 1]);
@@ -941,7 +973,7 @@ __global__ __launch_bounds__(256) void k_nodes_internal(const Counts* __restrict
 }
 
 template <typename T4>
-__global__ __launch_bounds__(256) void k_nodes_leaf(const Counts* __restrict__ cnt, const Cube* __restrict__ cubes,
+__global__ __launch_bounds__(256) void k_nodes_leaf(Counts* __restrict__ cnt, const Cube* __restrict__ cubes,
                                                     const int32_t* __restrict__ ucid,
                                                     const int32_t* __restrict__ split,
                                                     const int32_t* __restrict__ nstart,
@@ -951,6 +983,7 @@ __global__ __launch_bounds__(256) void k_nodes_leaf(const Counts* __restrict__ c
                                                     int32_t* __restrict__ nx, uint8_t* __restrict__ nlev, int nmax) {
   int x = blockIdx.x * blockDim.x + threadIdx.x;
   const int U = cnt->n_unique;
+  if (x == 0) cnt->n_nodes = U + cnt->n_internal;
   if (x >= nmax || x >= U) return;
   const int pre = x + nexcl[x] + nstart[x];
   Mom mo;
@@ -1269,7 +1302,7 @@ __device__ __forceinline__ void clear_sort(int32_t* __restrict__ hist, int32_t* 
                                            uint32_t* __restrict__ tiles, int64_t words) {
   const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = i0; i < kSortPasses * 256; i += step) hist[i] = 0;
-  if (i0 < kSortPasses) ticket[i0] = 0;
+  if (i0 <= kSortPasses) ticket[i0] = 0;
   for (int64_t i = i0; i < words; i += step) tiles[i] = 0;
 }
 
@@ -1342,22 +1375,18 @@ static hipError_t build_impl(const T* pos, const T* mass, int n, const BuildWs& 
     if ((e = hilbert_impl<T4>(n, w, fork->side)) != hipSuccess) return e;
     if ((e = hipEventRecord(fork->join, fork->side)) != hipSuccess) return e;
   }
-  // unique (cluster, key) pairs
-  k_unique_flags<<<nblk(n, 256), 256, 0, st>>>(w.key_a, scid, n, w.flag);
-  if ((e = scan_excl(w.flag, w.uid, n, w.scan_tiles, nullptr, st)) != hipSuccess) return e;
-  k_unique_write<<<nblk(n, 256), 256, 0, st>>>(w.key_a, scid, n, w.flag, w.uid, w.ukey, w.ustart, ucid,
-                                               w.counts, w.nstart, w.lmask);
-  k_croot_first<<<nblk(K + 1, 256), 256, 0, st>>>(w.seg_off, K, n, w.uid, w.counts, w.croot);
+  // unique (cluster, key) pairs (the sort's last pass left the words of its next one cleared)
+  const int ut = unique_tiles(n);
+  k_unique<<<ut, kSortThreads, 0, st>>>(w.key_a, scid, n, K, w.ukey, w.ustart, ucid, w.counts, w.nstart, w.lmask,
+                                        w.croot, sc.tiles[(8 + seg_passes) & 1], w.ticket + kSortPasses, ut);
   // internal nodes
-  k_pairs<<<nblk(n, 256), 256, 0, st>>>(w.ukey, ucid, w.croot, w.counts, w.split, w.flag, w.pf, w.pl, n);
-  if ((e = scan_excl(w.flag, w.uid, n, w.scan_tiles, nullptr, st)) != hipSuccess) return e;
-  k_internal_write<<<nblk(n, 256), 256, 0, st>>>(w.flag, w.uid, w.split, w.pf, w.pl, w.counts, w.ilevel, w.ifirst,
-                                                 w.ilast, w.nstart, w.lmask, n);
-  if ((e = scan_excl(w.nstart, w.nexcl, n + 1, w.scan_tiles, nullptr, st)) != hipSuccess) return e;
+  k_pairs<<<nblk(n, 256), 256, 0, st>>>(w.ukey, ucid, w.croot, w.counts, w.split, w.flag, w.pf, w.pl, w.nstart, w.lmask,
+                                        n);
+  if ((e = scan_excl(w.nstart, w.nexcl, n + 1, w.scan_tiles, &w.counts->n_internal, st)) != hipSuccess) return e;
   k_croot_final<<<nblk(K + 1, 256), 256, 0, st>>>(K, w.nexcl, w.croot);
-  k_nodes_internal<T4><<<nblk(n, 256), 256, 0, st>>>(w.counts, w.cube, ucid, w.ilevel, w.ifirst, w.ilast,
-                                                     w.nstart, w.nexcl, w.lmask, w.ustart, w.ukey, w.nodes, w.nx,
-                                                     w.nlev, w.seg_off, w.croot, w.anc, n);
+  k_nodes_internal<<<nblk(n, 256), 256, 0, st>>>(w.counts, w.cube, ucid, w.flag, w.split, w.pf, w.pl, w.nstart, w.nexcl,
+                                                 w.lmask, w.ustart, w.ukey, w.nodes, w.nx, w.nlev, w.seg_off, w.croot,
+                                                 w.anc, n);
   k_nodes_leaf<T4><<<nblk(n, 256), 256, 0, st>>>(w.counts, w.cube, ucid, w.split, w.nstart, w.nexcl, w.ustart,
                                                  reinterpret_cast<const T4*>(w.ps), w.nodes, w.mom, w.nx, w.nlev, n);
   // moments: chunks of the preorder (2n nodes at most), then the straddling

@@ -1,5 +1,6 @@
-"""The build's radix sort at the edges of its tiles and of its tile sizes: the particle order against a
-stable sort of the keys' definition in numpy (exact), for one tree and for forests."""
+"""The build's radix sort and its pass over the unique keys at the edges of their tiles and tile sizes: the
+particle order against a stable sort of the keys' definition in numpy, and the leaf counts (exact), for one
+tree and for forests."""
 import numpy as np
 import pytest
 import torch
@@ -33,8 +34,8 @@ def _order(pos, off):
 
 
 @pytest.mark.parametrize("kind", ["random", "few"])
-@pytest.mark.parametrize("n", [4097, 5119, 5120, 5121, (1 << 18) - 1, 1 << 18, (1 << 18) + 1, (1 << 21) - 3, 1 << 21,
-                               (1 << 21) + 1])
+@pytest.mark.parametrize("n", [4097, 5119, 5120, 5121, (1 << 17) - 1, 1 << 17, (1 << 17) + 1, (1 << 19) - 3, 1 << 19,
+                               (1 << 19) + 1, 3000001])
 def test_sorted_order(bh, n, kind):
     print(f"[sort] n={n} {kind}", flush=True)
     rng = np.random.default_rng(n)
@@ -44,6 +45,7 @@ def test_sorted_order(bh, n, kind):
     for _ in range(2):          # a rebuild in the same workspace meets the words of the last one
         _, perm = T.export()
         np.testing.assert_array_equal(perm, _order(pos, [0, n]))
+        assert T.stats()["n_leaves"] == len(np.unique(_keys(pos)))
         T = bh.Tree(T.pos, T.mass, T.workspace)
     w = T.walk_order().cpu().numpy()
     np.testing.assert_array_equal(np.sort(w), np.arange(n))
@@ -61,3 +63,8 @@ def test_sorted_order_forest(bh, K, per):
     _, perm = T.export()
     np.testing.assert_array_equal(perm, _order(pos.astype(np.float64), off))
     np.testing.assert_array_equal(np.sort(T.walk_order().cpu().numpy()), np.arange(off[-1]))
+    leaves = [len(np.unique(_keys(pos[b:e].astype(np.float64)))) if e > b else 0 for b, e in zip(off[:-1], off[1:])]
+    assert T.stats()["n_leaves"] == sum(leaves)
+    roots = T.roots().cpu().numpy()
+    for k, u in enumerate(leaves):
+        assert (roots[k + 1] - roots[k] > 0) == (u > 0)

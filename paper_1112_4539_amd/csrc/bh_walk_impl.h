@@ -979,11 +979,14 @@ __global__ __launch_bounds__(256) void k_walk(WalkArgs a) {
   walk_group<kF64, kT, kMode, kSoft, kGroupTheta, false>(a, blk * a.waves_per_block + wv, pf_lds[wv], nullptr);
 }
 
-// The same where clusters have several runs.  (FP32 with one theta is asked for
-// 8 waves per SIMD: left alone it takes two vector registers too many for that.)
+// The same where clusters have several runs, or with two targets per lane.
+// (FP32 of order 1 is asked for 8 waves per SIMD: left alone it takes a few
+// vector registers too many for that.  Order 2 has the vector registers but not
+// the scalars, which then move to vector lanes inside its step loop: a forest of
+// 30 clusters 2.66 -> 4.19 ms.)
 template <bool kF64, int kT, int kMode, bool kSoft, bool kGroupTheta>
 __global__ __launch_bounds__(256)
-__attribute__((amdgpu_waves_per_eu(!kF64 && kT == 1 && kMode == kWalkForces && !kGroupTheta ? 8 : 1)))
+__attribute__((amdgpu_waves_per_eu(!kF64 && kT == 1 && kMode == kWalkForces ? 8 : 1)))
 void k_walk_runs(WalkArgs a) {
   __shared__ uint4 pf_lds[4][2][8];
   extern __shared__ double dyn_lds[];  // per wave: the totals of its targets
@@ -1037,9 +1040,9 @@ static hipError_t launch_t(const WalkArgs& a, hipStream_t st) {
     hipError_t e = fill_i32(a.queue, 1, 0, st);
     if (e != hipSuccess) return e;
     k_walk_persistent<kF64, kT, kMode, kSoft, kGroupTheta><<<max(1, min(a.grid, blocks)), wpb * kWave, lds, st>>>(a);
-  } else if (a.max_runs > 1 || kT != 1 || (kMode & 3) != kWalkForces) {
+  } else if (a.max_runs > 1 || kT != 1) {
     k_walk_runs<kF64, kT, kMode, kSoft, kGroupTheta><<<blocks, wpb * kWave, lds, st>>>(a);
-  } else if constexpr (kT == 1 && (kMode & 3) == kWalkForces) {
+  } else if constexpr (kT == 1) {
     k_walk<kF64, kT, kMode, kSoft, kGroupTheta><<<blocks, wpb * kWave, 0, st>>>(a);
   }
   return hipGetLastError();

@@ -1572,7 +1572,7 @@ struct SmallLds {
 static_assert(sizeof(SmallLds) <= 160 * 1024, "the small build's arrays must fit the LDS");
 
 // One stable pass by the 8-bit digit at `shift`, buffer b to buffer b ^ 1: each
-// wave ranks its contiguous share in input order (as k_rs_scatter does), then
+// wave ranks its contiguous share in input order (as k_rs_pass does), then
 // the counts are scanned digit by digit, wave by wave.
 __device__ __forceinline__ void small_sort_pass(SmallLds& s, int n, int shift, int b) {
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;

@@ -97,8 +97,7 @@ size_t layout(int64_t n, int64_t K, int prec, char* base, bh::BuildWs* w, int32_
   t.seg = reinterpret_cast<int32_t*>(take(4 * N));
   t.scid = reinterpret_cast<int32_t*>(take(4 * N));
   t.ucid = reinterpret_cast<int32_t*>(take(4 * N));
-  t.bbox_part = reinterpret_cast<double*>(take(sizeof(double) * 6 * bh::kBboxBlocks));
-  t.n_bbox_blocks = bh::kBboxBlocks;
+  t.bbox_part = reinterpret_cast<double*>(take(sizeof(double) * 7 * bh::kBboxBlocks));
   t.key_a = reinterpret_cast<uint64_t*>(take(8 * N));
   t.key_b = reinterpret_cast<uint64_t*>(take(8 * N));
   t.ukey = reinterpret_cast<uint64_t*>(take(8 * N));

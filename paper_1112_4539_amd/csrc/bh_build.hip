@@ -172,11 +172,56 @@ hipError_t scan_excl(const int32_t* in, int32_t* out, int n, int32_t* tile_buf, 
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------- start of a build
+// What a sort needs beside its keys: the passes' histograms and tickets, and two
+// tables of tile words, which the passes use in turn (each clears the other's
+// for the next one).
+struct SortScratch {
+  int32_t* hist;     // [kSortPasses][256]
+  int32_t* ticket;   // [kSortPasses]
+  uint32_t* tiles[2];
+};
+
+__device__ __forceinline__ void clear_sort(int32_t* __restrict__ hist, int32_t* __restrict__ ticket,
+                                           uint32_t* __restrict__ tiles, int64_t words) {
+  const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = i0; i < kSortPasses * 256; i += step) hist[i] = 0;
+  if (i0 <= kSortPasses) ticket[i0] = 0;
+  for (int64_t i = i0; i < words; i += step) tiles[i] = 0;
+}
+
+__global__ __launch_bounds__(256) void k_clear_sort(int32_t* __restrict__ hist, int32_t* __restrict__ ticket,
+                                                    uint32_t* __restrict__ tiles, int64_t words) {
+  clear_sort(hist, ticket, tiles, words);
+}
+
+// The start of a build: counters, offsets, the sort's words, run ancestors, and
+// cluster roots for an empty build (every cluster starts and ends at node 0).
+// By every thread of a launch.
+__device__ __forceinline__ void init_build(const BuildWs& w, const SortScratch& sc, int64_t n, int64_t words,
+                                           int64_t n_anc) {
+  const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+  if (i0 < (int64_t)(sizeof(Counts) / 4)) reinterpret_cast<int32_t*>(w.counts)[i0] = 0;
+  if (w.seg_off == w.own_off && i0 < 2) w.own_off[i0] = i0 ? n : 0;
+  for (int64_t i = i0; i <= w.n_seg; i += step) w.croot[i] = 0;
+  for (int64_t i = i0; i < n_anc; i += step) w.anc[i] = -1;
+  if (words) clear_sort(sc.hist, sc.ticket, sc.tiles[0], words);
+}
+
+__global__ __launch_bounds__(256) void k_init(BuildWs w, SortScratch sc, int64_t n, int64_t words, int64_t n_anc) {
+  init_build(w, sc, n, words, n_anc);
+}
+
 // ---------------------------------------------------------------- bbox
+// Per workgroup the coordinate-wise extremes and whether an input is not finite
+// (w.bbox_part [7][gridDim.x]).  The launch also starts the build: nothing else
+// reads or counts into what init_build clears before the next launch.  (A launch
+// of its own for that took 5 to 6 us of every build.)
 template <typename T>
 __global__ __launch_bounds__(256) void k_bbox_partial(const T* __restrict__ pos, const T* __restrict__ mass,
-                                                      int64_t n, double* __restrict__ part,
-                                                      Counts* __restrict__ cnt) {
+                                                      int64_t n, BuildWs ws, SortScratch sc, int64_t words,
+                                                      int64_t n_anc) {
+  init_build(ws, sc, n, words, n_anc);
   __shared__ double red[6][4];
   double mn[3] = {INFINITY, INFINITY, INFINITY};
   double mx[3] = {-INFINITY, -INFINITY, -INFINITY};
@@ -194,7 +239,7 @@ __global__ __launch_bounds__(256) void k_bbox_partial(const T* __restrict__ pos,
     }
     if (!isfinite((double)mass[i])) bad = true;
   }
-  if (__any(bad) && lane_id() == 0) atomicOr(&cnt->bad_input, 1);
+  bad = __syncthreads_or(bad);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
@@ -213,8 +258,9 @@ __global__ __launch_bounds__(256) void k_bbox_partial(const T* __restrict__ pos,
     int k = threadIdx.x;
     double v = red[k][0];
     for (int q = 1; q < 4; ++q) v = (k < 3) ? fmin(v, red[k][q]) : fmax(v, red[k][q]);
-    part[blockIdx.x * 6 + k] = v;
+    ws.bbox_part[k * gridDim.x + blockIdx.x] = v;
   }
+  if (threadIdx.x == 6) ws.bbox_part[6 * gridDim.x + blockIdx.x] = bad ? 1.0 : 0.0;
 }
 
 // Root cube from the coordinate-wise extremes: lo = minimum corner, side L =
@@ -235,20 +281,32 @@ __device__ void finish_cube(double lo[3], double hi[3], Cube* __restrict__ cube)
   cube->scale = (double)kGrid / L;
 }
 
-// One wave folds the per-block extremes (min and max are exact, so the order
-// does not matter).
-__global__ __launch_bounds__(64) void k_bbox_final(const double* __restrict__ part, int nb, Cube* __restrict__ cube) {
-  const int lane = threadIdx.x;
-  double v[6];
-  for (int k = 0; k < 6; ++k) v[k] = k < 3 ? INFINITY : -INFINITY;
-  for (int b = lane; b < nb; b += 64)
-    for (int k = 0; k < 6; ++k) v[k] = k < 3 ? fmin(v[k], part[b * 6 + k]) : fmax(v[k], part[b * 6 + k]);
-  for (int k = 0; k < 6; ++k)
-    for (int o = 32; o > 0; o >>= 1) {
-      double u = __shfl_xor(v[k], o, 64);
-      v[k] = k < 3 ? fmin(v[k], u) : fmax(v[k], u);
-    }
-  if (lane == 0) finish_cube(v, v + 3, cube);
+// One wave per row of the workgroups' extremes (min and max are exact, so the
+// order does not matter); the last finds the inputs that are not finite.  (One
+// wave for all rows, in turn, took 8.5 us.)
+__global__ __launch_bounds__(448) void k_bbox_final(const double* __restrict__ part, int nb, Cube* __restrict__ cube,
+                                                    Counts* __restrict__ cnt) {
+  __shared__ double ext[6];
+  const int lane = threadIdx.x & 63, k = threadIdx.x >> 6;
+  double v = k < 3 ? INFINITY : -INFINITY;
+#pragma unroll 4
+  for (int b = lane; b < nb; b += 64) v = k < 3 ? fmin(v, part[k * nb + b]) : fmax(v, part[k * nb + b]);
+  for (int o = 32; o > 0; o >>= 1) {
+    const double u = __shfl_xor(v, o, 64);
+    v = k < 3 ? fmin(v, u) : fmax(v, u);
+  }
+  if (lane == 0) {
+    if (k < 6)
+      ext[k] = v;
+    else if (v > 0.0)
+      atomicOr(&cnt->bad_input, 1);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double e[6];
+    for (int q = 0; q < 6; ++q) e[q] = ext[q];
+    finish_cube(e, e + 3, cube);
+  }
 }
 
 // Offsets of a forest: off[0] = 0, nondecreasing, off[K] = n.  A violation is
@@ -554,15 +612,6 @@ __device__ __forceinline__ void store_digits(uint32_t (*h)[256], int passes, int
 // few large ones.
 constexpr int kKeyThreads = 512;
 static inline int key_blocks(int64_t n) { return (int)min((int64_t)512, max((int64_t)1, (n + 2047) / 2048)); }
-
-// What a sort needs beside its keys: the passes' histograms and tickets, and two
-// tables of tile words, which the passes use in turn (each clears the other's
-// for the next one).
-struct SortScratch {
-  int32_t* hist;     // [kSortPasses][256]
-  int32_t* ticket;   // [kSortPasses]
-  uint32_t* tiles[2];
-};
 
 template <int kDig>
 static void launch_pass(const uint64_t* kin, const int32_t* vin, const BuildWs& w, uint64_t* kout, int32_t* vout, int n,
@@ -1298,28 +1347,6 @@ static inline int nblk(int64_t n, int t) { return (int)((n + t - 1) / t) > 0 ? (
 template <typename T4>
 static hipError_t hilbert_impl(int n, const BuildWs& w, hipStream_t st);
 
-__device__ __forceinline__ void clear_sort(int32_t* __restrict__ hist, int32_t* __restrict__ ticket,
-                                           uint32_t* __restrict__ tiles, int64_t words) {
-  const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = i0; i < kSortPasses * 256; i += step) hist[i] = 0;
-  if (i0 <= kSortPasses) ticket[i0] = 0;
-  for (int64_t i = i0; i < words; i += step) tiles[i] = 0;
-}
-
-__global__ __launch_bounds__(256) void k_clear_sort(int32_t* __restrict__ hist, int32_t* __restrict__ ticket,
-                                                    uint32_t* __restrict__ tiles, int64_t words) {
-  clear_sort(hist, ticket, tiles, words);
-}
-
-__global__ __launch_bounds__(256) void k_init(BuildWs w, SortScratch sc, int64_t n, int64_t words, int64_t n_anc) {
-  const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
-  if (i0 < (int64_t)(sizeof(Counts) / 4)) reinterpret_cast<int32_t*>(w.counts)[i0] = 0;
-  if (w.seg_off == w.own_off && i0 < 2) w.own_off[i0] = i0 ? n : 0;
-  for (int64_t i = i0; i <= w.n_seg; i += step) w.croot[i] = 0;
-  for (int64_t i = i0; i < n_anc; i += step) w.anc[i] = -1;
-  if (words) clear_sort(sc.hist, sc.ticket, sc.tiles[0], words);
-}
-
 static inline int clear_blocks(int64_t n) { return (int)min((int64_t)1024, max((int64_t)8, n / 4096)); }
 
 template <typename T, typename T4>
@@ -1327,22 +1354,21 @@ static hipError_t build_impl(const T* pos, const T* mass, int n, const BuildWs& 
                              hipStream_t st) {
   hipError_t e;
   const int K = w.n_seg;
-  // counters, offsets, the sort's words, run ancestors, and cluster roots for an
-  // empty build (every cluster starts and ends at node 0)
+  // the start, and the root cubes (of one cluster: in the launch of the start)
   {
     const SortScratch sc{w.hist, w.ticket, {w.tiles, nullptr}};
-    k_init<<<clear_blocks(n), 256, 0, st>>>(w, sc, n, n > 0 ? 256 * sort_tiles(n) : 0,
-                                            w.anc ? (int64_t)K * kMaxRuns * kAncSlots : 0);
-  }
-  if (w.seg_off != w.own_off) k_seg_check<<<nblk(K + 1, 256), 256, 0, st>>>(w.seg_off, K, n, w.counts);
-  if (n == 0) return hipGetLastError();
-  // root cubes
-  if (K == 1) {
-    const int nbb = w.n_bbox_blocks;
-    k_bbox_partial<T><<<nbb, 256, 0, st>>>(pos, mass, n, w.bbox_part, w.counts);
-    k_bbox_final<<<1, 64, 0, st>>>(w.bbox_part, nbb, w.cube);
-  } else {
-    k_bbox_seg<T><<<K, 256, 0, st>>>(pos, mass, w.seg_off, n, w.cube, w.counts);
+    const int64_t words = n > 0 ? 256 * sort_tiles(n) : 0, n_anc = w.anc ? (int64_t)K * kMaxRuns * kAncSlots : 0;
+    const int nbb = min(kBboxBlocks, nblk(n, 256));
+    if (K == 1 && n > 0)
+      k_bbox_partial<T><<<nbb, 256, 0, st>>>(pos, mass, n, w, sc, words, n_anc);
+    else
+      k_init<<<clear_blocks(n), 256, 0, st>>>(w, sc, n, words, n_anc);
+    if (w.seg_off != w.own_off) k_seg_check<<<nblk(K + 1, 256), 256, 0, st>>>(w.seg_off, K, n, w.counts);
+    if (n == 0) return hipGetLastError();
+    if (K == 1)
+      k_bbox_final<<<1, 448, 0, st>>>(w.bbox_part, nbb, w.cube, w.counts);
+    else
+      k_bbox_seg<T><<<K, 256, 0, st>>>(pos, mass, w.seg_off, n, w.cube, w.counts);
   }
   // keys and stable sort by (cluster, key): 8 key passes, then the cluster digits
   // cluster ids are kept only for a forest (a single tree's are all 0)

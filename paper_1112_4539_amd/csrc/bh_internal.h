@@ -79,8 +79,7 @@ struct BuildWs {
   int32_t* scid;            // [n] Morton position -> cluster
   int32_t* ucid;            // [n] unique key -> cluster
   int32_t* croot;           // [K+1] preorder id of each cluster's root; croot[K] = node count
-  double* bbox_part;        // [kBboxBlocks][6]
-  int n_bbox_blocks;
+  double* bbox_part;        // [7][kBboxBlocks]
   uint64_t *key_a, *key_b;  // [n]
   int32_t *idx_a, *idx_b;   // [n]; idx_a ends as perm (Morton position -> caller index)
   int32_t* hist;            // [kSortPasses][256] digit counts of the sort's passes

@@ -148,7 +148,7 @@ struct NbrArgs {
   int n_seg;
   int n;
   double r2;                   // r^2
-  float r2f;                   // FP32 bound above r^2 for the filter of FP32 trees (+inf: let all pass)
+  float r2f;                   // FP32 bound above r^2 for the filter of FP32 trees (+inf: every pair passes)
   double inv_h;                // 1/h, h = r/2
   double sig;                  // 1/(pi h^3), the spline's normalisation
   int32_t* count;              // [n] neighbours, caller order
@@ -213,7 +213,9 @@ __device__ __forceinline__ void nbr_pair(const NbrArgs& a, NbrTarget& T, int idx
 // is near any of them.  The test of FP32 trees is a filter in FP32, 7
 // instructions instead of 10: its squared distance is within 2^-21 of the exact
 // one (three rounded differences, squared and summed), so a bound 2^-20 above
-// r^2 lets every neighbour pass; what passes takes the exact test in FP64.
+// r^2 lets every neighbour pass; what passes takes the exact test in FP64.  It
+// compares with "less or equal": FP32 distances beyond 1.84e19 have a square of
+// +inf, which has to pass a bound of +inf.
 template <bool kF64, bool kLists, bool kOff32>
 __device__ __forceinline__ void nbr_group(const NbrArgs& a, NbrTarget& T, int idx0, bool in, int first, int count) {
   typedef float v16f_t __attribute__((ext_vector_type(16)));
@@ -250,7 +252,7 @@ __device__ __forceinline__ void nbr_group(const NbrArgs& a, NbrTarget& T, int id
         m[j] = __builtin_amdgcn_fcmp(fma(dz, dz, fma(dy, dy, dx * dx)), bound, 4);  // ordered <
       } else {
         const float dx = q[4 * j] - xi, dy = q[4 * j + 1] - yi, dz = q[4 * j + 2] - zi;
-        m[j] = __builtin_amdgcn_fcmpf(fmaf(dz, dz, fmaf(dy, dy, dx * dx)), bound, 4);
+        m[j] = __builtin_amdgcn_fcmpf(fmaf(dz, dz, fmaf(dy, dy, dx * dx)), bound, 5);  // ordered <=
       }
       any |= m[j];
     }
@@ -392,8 +394,9 @@ hipError_t launch_neighbours(bool f64, const Node* nodes, const Counts* counts, 
   a.n_seg = n_seg;
   a.n = n;
   a.r2 = radius * radius;
-  // the filter's bound: 2^-20 above r^2, where FP32 squares neither overflow nor
-  // lose anything that counts against r^2; outside that range everything passes
+  // the filter's bound: 2^-20 above r^2 where an FP32 square that overflows is
+  // beyond r^2 and one that loses bits to underflow is far below it; outside that
+  // range +inf, which no square exceeds
   a.r2f = radius > 1e-15 && radius < 1e15 ? (float)(a.r2 * (1.0 + 0x1p-20)) : __builtin_huge_valf();
   const double h = 0.5 * radius;
   a.inv_h = 1.0 / h;

@@ -93,6 +93,7 @@ size_t layout(int64_t n, int64_t K, int prec, char* base, bh::BuildWs* w, int32_
   t.own_off = reinterpret_cast<int64_t*>(take(2 * sizeof(int64_t)));
   t.seg_off = t.own_off;
   t.croot = reinterpret_cast<int32_t*>(take(4 * ((size_t)K + 1)));
+  t.cfirst = reinterpret_cast<int32_t*>(take(4 * ((size_t)K + 1)));
   int32_t* q = reinterpret_cast<int32_t*>(take(4));
   t.seg = reinterpret_cast<int32_t*>(take(4 * N));
   t.scid = reinterpret_cast<int32_t*>(take(4 * N));
@@ -332,6 +333,7 @@ int run_walk(const bh_tree* t, double theta, const float* theta_group, double ep
   a.order = walk_order_of(t);
   a.scid = t->n_seg > 1 ? t->w.scid : nullptr;  // (a single tree keeps no cluster ids)
   a.croot = t->w.croot;
+  a.cfirst = t->w.cfirst;
   a.seg_off = t->w.seg_off;
   a.n_seg = (int)t->n_seg;
   a.n = (int)t->n;

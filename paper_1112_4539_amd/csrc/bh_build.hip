@@ -783,12 +783,15 @@ __global__ __launch_bounds__(kSortThreads) void k_unique(const uint64_t* __restr
 
 // Preorder id of the cluster's root: the shallowest node starting at its first
 // unique key u, u + #internal nodes starting before u; for k = K the node count.
+// And the cluster's first particle; for k = K the particle count.
 __global__ __launch_bounds__(256) void k_croot_final(int K, const int32_t* __restrict__ nexcl,
-                                                     int32_t* __restrict__ croot) {
+                                                     const int32_t* __restrict__ ustart, int32_t* __restrict__ croot,
+                                                     int32_t* __restrict__ cfirst) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k > K) return;
   const int u = croot[k];
   croot[k] = u + nexcl[u];
+  cfirst[k] = ustart[u];
 }
 
 // ---------------------------------------------------------------- topology
@@ -1003,8 +1006,8 @@ __global__ __launch_bounds__(256) void k_nodes_internal(const Counts* __restrict
                                                         const int32_t* __restrict__ ustart,
                                                         const uint64_t* __restrict__ ukey, Node* __restrict__ nodes,
                                                         int32_t* __restrict__ nx, uint8_t* __restrict__ nlev,
-                                                        const int64_t* __restrict__ seg_off,
                                                         const int32_t* __restrict__ croot,
+                                                        const int32_t* __restrict__ cfirst,
                                                         int32_t* __restrict__ anc, int nmax) {
   // (a thread per pair of adjacent unique keys; the pairs that stand for a cell)
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1018,7 +1021,7 @@ __global__ __launch_bounds__(256) void k_nodes_internal(const Counts* __restrict
   nlev[pre] = (uint8_t)s;
   if (anc)
     list_ancestor(anc + (int64_t)cl * kMaxRuns * kAncSlots, croot[cl], croot[cl + 1],
-                  walk_segments(cluster_size(seg_off, cl, nmax)), pre, nd.next, s);
+                  walk_segments(cfirst[cl + 1] - cfirst[cl]), pre, nd.next, s);
 }
 
 template <typename T4>
@@ -1409,9 +1412,9 @@ static hipError_t build_impl(const T* pos, const T* mass, int n, const BuildWs& 
   k_pairs<<<nblk(n, 256), 256, 0, st>>>(w.ukey, ucid, w.croot, w.counts, w.split, w.flag, w.pf, w.pl, w.nstart, w.lmask,
                                         n);
   if ((e = scan_excl(w.nstart, w.nexcl, n + 1, w.scan_tiles, &w.counts->n_internal, st)) != hipSuccess) return e;
-  k_croot_final<<<nblk(K + 1, 256), 256, 0, st>>>(K, w.nexcl, w.croot);
+  k_croot_final<<<nblk(K + 1, 256), 256, 0, st>>>(K, w.nexcl, w.ustart, w.croot, w.cfirst);
   k_nodes_internal<<<nblk(n, 256), 256, 0, st>>>(w.counts, w.cube, ucid, w.flag, w.split, w.pf, w.pl, w.nstart, w.nexcl,
-                                                 w.lmask, w.ustart, w.ukey, w.nodes, w.nx, w.nlev, w.seg_off, w.croot,
+                                                 w.lmask, w.ustart, w.ukey, w.nodes, w.nx, w.nlev, w.croot, w.cfirst,
                                                  w.anc, n);
   k_nodes_leaf<T4><<<nblk(n, 256), 256, 0, st>>>(w.counts, w.cube, ucid, w.split, w.nstart, w.nexcl, w.ustart,
                                                  reinterpret_cast<const T4*>(w.ps), w.nodes, w.mom, w.nx, w.nlev, n);
@@ -1662,7 +1665,7 @@ struct SmallArgs {
   Counts* counts;
   const int64_t* seg_off;  // the caller's offsets {0, n}, to be checked (null: none)
   int64_t* own_off;        // the tree's own, to be written
-  int32_t* croot;
+  int32_t *croot, *cfirst;
   int32_t* perm;
   void* ps;
   Node* nodes;
@@ -1857,6 +1860,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(const T* __restri
       s.start[kLevels + 1] = run;
       a.croot[0] = 0;
       a.croot[1] = U + I;
+      a.cfirst[0] = 0;
+      a.cfirst[1] = n;
       *a.cube = cube;
       Counts cn{};
       cn.n_unique = U;
@@ -1936,8 +1941,9 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(const T* __restri
 template <typename T, typename T4>
 static hipError_t build_small_impl(const T* pos, const T* mass, int n, const BuildWs& w, hipStream_t st) {
   if (n < 1 || n > kSmallBuild || w.n_seg != 1 || !w.anc) return hipErrorInvalidValue;
-  SmallArgs a{n,      w.cube, w.counts, w.seg_off == w.own_off ? nullptr : w.seg_off, w.own_off, w.croot, w.idx_a, w.ps,
-              w.nodes, w.mom,  w.nx,     w.nlev, w.obkt, w.okids, w.anc, w.horder, (int)n_chunks(n), hilbert_levels(1)};
+  SmallArgs a{n,       w.cube, w.counts, w.seg_off == w.own_off ? nullptr : w.seg_off, w.own_off, w.croot, w.cfirst,
+              w.idx_a, w.ps,   w.nodes,  w.mom, w.nx, w.nlev, w.obkt, w.okids, w.anc, w.horder, (int)n_chunks(n),
+              hilbert_levels(1)};
   k_build_small<T, T4><<<1, kSmallThreads, 0, st>>>(pos, mass, a);
   return hipGetLastError();
 }

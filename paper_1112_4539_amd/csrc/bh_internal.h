@@ -47,7 +47,9 @@ inline int n_super(int64_t n) { return (int)((n_chunks(n) + kSuperChunks - 1) / 
 // Runs of a cluster's subtree: a walk sums a target's terms run by run (equally
 // many preorder nodes each) and adds the runs' sums in order.  Several waves can
 // then share a group's walk; the cuts depend on the cluster's size alone, so
-// that a cluster's results do not depend on how it is walked.  More runs balance
+// that a cluster's results do not depend on how it is walked.  The size is the
+// tree's own (BuildWs::cfirst): the caller's offsets may be wrong, and the walk's
+// LDS is laid out for a single tree's runs.  More runs balance
 // the waves better (the run next to a group's targets holds the most work); what
 // limits them is that the workgroups a CU needs at once keep their runs' sums, 2
 // KB each, in its LDS: two workgroups up to 32,768 particles, four up to 65,536,
@@ -58,12 +60,6 @@ constexpr int kAncClusters = 1024;     // forests of at most this many clusters 
 constexpr int kMaxSplitWaves = 16;     // waves that share a group
 constexpr int64_t kSplitMaxN = 102400; // largest tree whose groups are shared (1600 groups)
 __host__ __device__ inline int walk_segments(int64_t n) { return n <= 32768 ? 36 : n <= 65536 ? 18 : n <= kSplitMaxN ? 10 : 1; }
-// Particles of cluster k (the offsets clamped to [0, n]).
-__host__ __device__ inline int64_t cluster_size(const int64_t* off, int k, int64_t n) {
-  const int64_t b = off[k] < 0 ? 0 : off[k] > n ? n : off[k];
-  const int64_t e = off[k + 1] < b ? b : off[k + 1] > n ? n : off[k + 1];
-  return e - b;
-}
 // Dynamic LDS of the one-wave-per-group walks: the totals of a wave's targets.
 inline size_t walk_lds(int waves_per_block, int targets_per_lane) {
   return (size_t)waves_per_block * targets_per_lane * 4 * kWave * sizeof(double);
@@ -79,6 +75,7 @@ struct BuildWs {
   int32_t* scid;            // [n] Morton position -> cluster
   int32_t* ucid;            // [n] unique key -> cluster
   int32_t* croot;           // [K+1] preorder id of each cluster's root; croot[K] = node count
+  int32_t* cfirst;          // [K+1] Morton position of each cluster's first particle; cfirst[K] = n
   double* bbox_part;        // [7][kBboxBlocks]
   uint64_t *key_a, *key_b;  // [n]
   int32_t *idx_a, *idx_b;   // [n]; idx_a ends as perm (Morton position -> caller index)
@@ -155,6 +152,7 @@ struct WalkArgs {
   const int32_t* order;        // optional target order (Morton positions), may be null
   const int32_t* scid;         // Morton position -> cluster (null for a single tree)
   const int32_t* croot;        // [K+1] preorder range of each cluster's subtree
+  const int32_t* cfirst;       // [K+1] Morton position of each cluster's first particle
   const int64_t* seg_off;      // [K+1] caller offsets of the clusters (list words are cluster-relative)
   const int32_t* anc;          // ancestors of the runs' first nodes (BuildWs::anc), may be null
   int n_seg;
@@ -180,7 +178,7 @@ struct WalkArgs {
   int grid;                    // persistent: workgroups launched
   int targets_per_lane;        // 1 or 2: a wave walks 64 or 128 targets
   int split_waves;             // > 1: the waves of a workgroup share one group's walk (forces, one target per lane)
-  int max_runs;                // the most runs a cluster of the tree can have
+  int max_runs;                // the most runs a cluster of the tree can have (what the walk's LDS holds)
 };
 
 enum WalkMode { kWalkForces = 0, kWalkStats = 1, kWalkDump = 2 };

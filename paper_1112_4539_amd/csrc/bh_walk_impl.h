@@ -600,6 +600,9 @@ __device__ __forceinline__ void walk_loop_lds(const WalkArgs& a, StepNode<kF64, 
 // cluster alone, so one wave that walks the runs one after the other (below)
 // and several that share them (walk_split) give the same bits.
 __device__ __forceinline__ int run_length(int r0, int r1, int runs) { return max(1, (r1 - r0 + runs - 1) / runs); }
+__device__ __forceinline__ int cluster_runs(const WalkArgs& a, int k) {
+  return min(uniform(walk_segments(a.cfirst[k + 1] - a.cfirst[k])), a.max_runs);
+}
 
 // The total of a wave's targets, in LDS between runs ([target of the lane][sum][lane]).
 template <int kT>
@@ -649,8 +652,7 @@ __device__ __forceinline__ void walk_clusters(const WalkArgs& a, StepNode<kF64, 
     if constexpr (!kRuns) {
       loop(r1);
     } else {
-      const int runs = uniform(walk_segments(cluster_size(a.seg_off, k, a.n)));
-      const int len = run_length(r0, r1, runs);
+      const int len = run_length(r0, r1, cluster_runs(a, k));
       for (int end = r0; C.c < r1;) {
         end = min(end + len, r1);
         if (C.c >= end) continue;
@@ -877,8 +879,8 @@ __device__ __forceinline__ void split_cluster(const WalkArgs& a, StepNode<kF64, 
   // of the work, and the longest pieces go first.
   const uint64_t m_mine = ballot(mine);
   const int at = m_mine ? __builtin_amdgcn_readlane(T.i, __builtin_ctzll(m_mine)) : 0;
-  const int64_t first = a.seg_off[k], size = max((int64_t)1, cluster_size(a.seg_off, k, a.n));
-  const int home = uniform((int)min(max((at - first) * runs / size, (int64_t)0), (int64_t)runs - 1));
+  const int first = a.cfirst[k], size = max(1, a.cfirst[k + 1] - first);
+  const int home = uniform((int)min(max((int64_t)(at - first) * runs / size, (int64_t)0), (int64_t)runs - 1));
   for (int turn = w; turn < runs;) {
     const int s = (home + ((turn & 1) ? (turn + 1) >> 1 : runs - (turn >> 1))) % runs;
     const int c0 = r0 + s * len, end = min(c0 + len, r1);
@@ -932,7 +934,7 @@ void k_walk_split(WalkArgs a) {
     const int cap = 2 * a.n;
     const int r0 = min(max(uniform(a.croot[k]), 0), cap);
     const int r1 = min(max(uniform(a.croot[k + 1]), r0), cap);
-    const int runs = uniform(walk_segments(cluster_size(a.seg_off, k, a.n)));
+    const int runs = cluster_runs(a, k);
     const bool mine = T.i >= 0 && G.kc[0] == k;
     if (threadIdx.x == 0) ticket = nw;
     __syncthreads();

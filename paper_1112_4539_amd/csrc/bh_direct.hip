@@ -39,15 +39,20 @@ struct DirectArgs {
 template <typename R>
 struct DirectSum {
   R ax, ay, az, p;
-  // One source: offset d, mass m (0: adds nothing).  kSoft: eps > 0, so r^2 > 0;
-  // without softening a pair at r = 0 adds nothing.
+  // One source: offset d, mass m.  kSoft: eps > 0, so r^2 > 0; without softening a
+  // pair at r = 0 adds nothing, whatever its mass (the test is one for zero: a
+  // position that is not a number has to reach the sums).
   template <bool kSoft>
   __device__ __forceinline__ void add(R dx, R dy, R dz, R m, R e2) {
     R ri;
     if constexpr (std::is_same<R, double>::value) {
       const double r2 = fma(dz, dz, fma(dy, dy, dx * dx)) + e2;
       ri = inv_sqrt_f64(r2);
-      if (!kSoft) ri = r2 > 0.0 ? ri : 0.0;
+      if (!kSoft) {
+        const bool none = r2 == 0.0;
+        ri = none ? 0.0 : ri;
+        m = none ? 0.0 : m;
+      }
     } else {
       const float r2 = fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, e2)));
       ri = __builtin_amdgcn_rsqf(r2);

@@ -127,9 +127,9 @@ struct AccF64 {
   // root.  (With IEEE square root and division and unfused sums a term took
   // about 50; build and walk of Plummer 1M at theta = 0.5 took 8.11 ms, 4.78 ms
   // now.)
-  template <bool kSoft>
+  // d2 + eps2 must not be 0 (it is not where the opening test passed, d2 > S >= 0).
   __device__ __forceinline__ void term(double dx, double dy, double dz, double d2, double m, double eps2) {
-    const double ri = inv_r<kSoft>(d2 + eps2);
+    const double ri = inv_sqrt_f64(d2 + eps2);
     const double mr = m * ri;
     const double mr3 = mr * (ri * ri);
     ax = fma(mr3, dx, ax);
@@ -138,10 +138,9 @@ struct AccF64 {
     p -= mr;
   }
   // Order-2 cell term: the monopole factors plus the correction of quad_part.
-  template <bool kSoft>
   __device__ __forceinline__ void term_quad(double dx, double dy, double dz, double d2, double m, double eps2,
                                             const QuadRec& q) {
-    const double ri = inv_r<kSoft>(d2 + eps2);
+    const double ri = inv_sqrt_f64(d2 + eps2);
     const QuadPart u = quad_part(dx, dy, dz, ri, q);
     const double mr = m * ri;
     const double c = fma(mr, ri * ri, u.c);
@@ -149,12 +148,6 @@ struct AccF64 {
     ay = fma(u.k, u.by, fma(c, dy, ay));
     az = fma(u.k, u.bz, fma(c, dz, az));
     p += u.pq - mr;
-  }
-  // r2 == 0 only for a coincident pair without softening: that pair adds nothing
-  template <bool kSoft>
-  static __device__ __forceinline__ double inv_r(double r2) {
-    const double ri = inv_sqrt_f64(r2);
-    return kSoft ? ri : (r2 > 0.0 ? ri : 0.0);
   }
 };
 
@@ -331,10 +324,12 @@ __device__ __forceinline__ void bucket_step(const WalkArgs& a, Cursor<kF64, kT>&
     Target<kF64>& T = C.t[t];
     if (T.skip <= c && C.k < C.kend && kk != T.i) {
       const double dx = (double)q.x - T.xi, dy = (double)q.y - T.yi, dz = (double)q.z - T.zi;
+      const double d2 = fma(dz, dz, fma(dy, dy, dx * dx));
       if constexpr (kF64) {
-        T.acc.template term<kSoft>(dx, dy, dz, fma(dz, dz, fma(dy, dy, dx * dx)), q.w, a.eps2);
+        // (a coincident pair without softening adds nothing, whatever its mass)
+        if (kSoft || d2 != 0.0) T.acc.term(dx, dy, dz, d2, q.w, a.eps2);
       } else {
-        T.acc.template term<kSoft>(dx, dy, dz, fma(dz, dz, fma(dy, dy, dx * dx)), q.w, a.eps2);
+        T.acc.template term<kSoft>(dx, dy, dz, d2, q.w, a.eps2);
       }
       if constexpr (kStats) {
         const uint64_t wd = (uint64_t)(a.perm[kk] - T.idx0) << 1;
@@ -487,9 +482,9 @@ __device__ __forceinline__ void walk_step(const WalkArgs& a, Cursor<kF64, kT>& C
       if (use[t]) {
         if constexpr (kF64) {
           if (quad)
-            T.acc.template term_quad<kSoft>(dx[t], dy[t], dz[t], d2[t], tm, a.eps2, qd);
+            T.acc.term_quad(dx[t], dy[t], dz[t], d2[t], tm, a.eps2, qd);
           else
-            T.acc.template term<kSoft>(dx[t], dy[t], dz[t], d2[t], tm, a.eps2);
+            T.acc.term(dx[t], dy[t], dz[t], d2[t], tm, a.eps2);
         } else {
           if (quad)
             T.acc.add_quad(q[t], u[t], dx[t], dy[t], dz[t]);

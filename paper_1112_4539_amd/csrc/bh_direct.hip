@@ -39,22 +39,23 @@ struct DirectArgs {
 template <typename R>
 struct DirectSum {
   R ax, ay, az, p;
-  // One source: offset d, mass m.  kSoft: eps > 0, so r^2 > 0; without softening a
-  // pair at r = 0 adds nothing, whatever its mass (the test is one for zero: a
-  // position that is not a number has to reach the sums).
+  // r^2 + eps^2 of a source at offset d.
+  static __device__ __forceinline__ R dist2(R dx, R dy, R dz, R e2) {
+    if constexpr (std::is_same<R, double>::value)
+      return fma(dz, dz, fma(dy, dy, dx * dx)) + e2;
+    else
+      return fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, e2)));
+  }
+  // One source: offset d, mass m.  kSoft: eps > 0, so r^2 > 0.  Without softening a
+  // pair at r = 0 adds nothing: in FP32 the root's place is taken by 0, in FP64
+  // the caller leaves the pair out, whatever its mass.
   template <bool kSoft>
   __device__ __forceinline__ void add(R dx, R dy, R dz, R m, R e2) {
+    const R r2 = dist2(dx, dy, dz, e2);
     R ri;
     if constexpr (std::is_same<R, double>::value) {
-      const double r2 = fma(dz, dz, fma(dy, dy, dx * dx)) + e2;
       ri = inv_sqrt_f64(r2);
-      if (!kSoft) {
-        const bool none = r2 == 0.0;
-        ri = none ? 0.0 : ri;
-        m = none ? 0.0 : m;
-      }
     } else {
-      const float r2 = fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, e2)));
       ri = __builtin_amdgcn_rsqf(r2);
       if (!kSoft) ri = r2 > 0.f ? ri : 0.f;
     }
@@ -70,6 +71,33 @@ struct DirectSum {
 };
 
 #define BH_CONST __attribute__((address_space(4)))
+
+// A batch of kBatch sources whose pairs at r = 0 are to be left out (FP64 without
+// softening): source k at q[3k..3k+2], not to be taken where own(k).  Such pairs
+// are rare, so that one branch for the wave tells batches without any; the test is
+// one for zero, since a position that is not a number has to reach the sums.
+template <int kBatch, typename Own>
+__device__ __forceinline__ void add_unequal(DirectSum<double>& s, const double* q, const double* m, double xi,
+                                            double yi, double zi, Own&& own) {
+  double dx[kBatch], dy[kBatch], dz[kBatch], r2[kBatch];
+  uint64_t out = 0;
+#pragma unroll
+  for (int k = 0; k < kBatch; ++k) {
+    dx[k] = q[3 * k] - xi;
+    dy[k] = q[3 * k + 1] - yi;
+    dz[k] = q[3 * k + 2] - zi;
+    r2[k] = DirectSum<double>::dist2(dx[k], dy[k], dz[k], 0.0);
+    out |= ballot(own(k)) | __builtin_amdgcn_fcmp(r2[k], 0.0, 1);  // ordered ==
+  }
+  if (out == 0ull) {
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) s.add<false>(dx[k], dy[k], dz[k], m[k], 0.0);
+  } else {
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k)
+      if (!own(k) && r2[k] != 0.0) s.add<false>(dx[k], dy[k], dz[k], m[k], 0.0);
+  }
+}
 
 template <bool kF64, bool kSoft, int kSub>
 __global__ __launch_bounds__(64 * kDirectMaxWaves) void k_direct(DirectArgs a) {
@@ -92,6 +120,7 @@ __global__ __launch_bounds__(64 * kDirectMaxWaves) void k_direct(DirectArgs a) {
   }
   const R e2 = (R)a.eps2;
   DirectSum<R> s{0, 0, 0, 0};
+  constexpr bool kUnequal = kF64 && !kSoft;
   const int len = (a.n + nw - 1) / nw;
   const int j0 = min(w * len, a.n), j1 = min(j0 + len, a.n);
   if constexpr (kSub == 1) {
@@ -106,7 +135,9 @@ __global__ __launch_bounds__(64 * kDirectMaxWaves) void k_direct(DirectArgs a) {
 #pragma unroll
       for (int k = 0; k < kBatch; ++k) m[k] = pm[(int64_t)j + k];
       // (a batch that holds a lane's own particle is rare: one test per batch)
-      if (ballot((unsigned)(i - j) < (unsigned)kBatch) == 0ull) {
+      if constexpr (kUnequal) {
+        add_unequal<kBatch>(s, q, m, xi, yi, zi, [&](int k) { return j + k == i; });
+      } else if (ballot((unsigned)(i - j) < (unsigned)kBatch) == 0ull) {
 #pragma unroll
         for (int k = 0; k < kBatch; ++k)
           s.template add<kSoft>(q[3 * k] - xi, q[3 * k + 1] - yi, q[3 * k + 2] - zi, m[k], e2);
@@ -118,7 +149,12 @@ __global__ __launch_bounds__(64 * kDirectMaxWaves) void k_direct(DirectArgs a) {
     }
     for (; j < j1; ++j) {
       const int64_t b = 3 * (int64_t)j;
-      if (j != i) s.template add<kSoft>(ps[b] - xi, ps[b + 1] - yi, ps[b + 2] - zi, pm[j], e2);
+      if constexpr (kUnequal) {
+        const R q[3] = {ps[b], ps[b + 1], ps[b + 2]}, m = pm[j];
+        add_unequal<1>(s, q, &m, xi, yi, zi, [&](int) { return j == i; });
+      } else {
+        if (j != i) s.template add<kSoft>(ps[b] - xi, ps[b + 1] - yi, ps[b + 2] - zi, pm[j], e2);
+      }
     }
   } else {
     constexpr int kBatch = 2;
@@ -133,13 +169,22 @@ __global__ __launch_bounds__(64 * kDirectMaxWaves) void k_direct(DirectArgs a) {
         q[3 * k + 2] = pos[3 * b + 2];
         m[k] = mass[b];
       }
+      if constexpr (kUnequal) {
+        add_unequal<kBatch>(s, q, m, xi, yi, zi, [&](int k) { return j + k * kSub == i; });
+      } else {
 #pragma unroll
-      for (int k = 0; k < kBatch; ++k)
-        if (j + k * kSub != i) s.template add<kSoft>(q[3 * k] - xi, q[3 * k + 1] - yi, q[3 * k + 2] - zi, m[k], e2);
+        for (int k = 0; k < kBatch; ++k)
+          if (j + k * kSub != i) s.template add<kSoft>(q[3 * k] - xi, q[3 * k + 1] - yi, q[3 * k + 2] - zi, m[k], e2);
+      }
     }
     for (; j < j1; j += kSub) {
       const int64_t b = 3 * (int64_t)j;
-      if (j != i) s.template add<kSoft>(pos[b] - xi, pos[b + 1] - yi, pos[b + 2] - zi, mass[j], e2);
+      if constexpr (kUnequal) {
+        const R q[3] = {pos[b], pos[b + 1], pos[b + 2]}, m = mass[j];
+        add_unequal<1>(s, q, &m, xi, yi, zi, [&](int) { return j == i; });
+      } else {
+        if (j != i) s.template add<kSoft>(pos[b] - xi, pos[b + 1] - yi, pos[b + 2] - zi, mass[j], e2);
+      }
     }
   }
   double v[4] = {(double)s.ax, (double)s.ay, (double)s.az, (double)s.p};

@@ -923,8 +923,10 @@ void k_walk_split(WalkArgs a) {
   Target<kF64>& T = C.t[0];
   const StepNode<kF64, kGroupTheta> wn = walk_nodes<kF64, kGroupTheta>(a);
   const bool buckets = uniform(a.cnt->n_unique < a.n ? 1 : 0) != 0;
-  constexpr bool kRaw = kF64 && kGroupTheta;
-  const bool off32 = !kRaw && a.n < kOff32MaxN;
+  // (the plain nodes of the FP64 per-group-theta walk keep 64-bit addressing;
+  // the others' copies are below 4 GiB in every tree whose groups are shared)
+  constexpr bool kOff32 = !(kF64 && kGroupTheta);
+  static_assert(kSplitMaxN < kOff32MaxN, "shared walks assume 32-bit record offsets");
   for (int k = G.klo; k <= G.khi; ++k) {
     const int cap = 2 * a.n;
     const int r0 = min(max(uniform(a.croot[k]), 0), cap);
@@ -934,17 +936,12 @@ void k_walk_split(WalkArgs a) {
     if (threadIdx.x == 0) ticket = nw;
     __syncthreads();
     if (r0 < r1) {
-#define BH_SPLIT(guard_, bucket_, off_) \
-  split_cluster<kF64, kMode, kSoft, kGroupTheta, guard_, bucket_, off_>(a, wn, C, k, r0, r1, runs, mine, w, &ticket, part)
-      if (off32) {
-        if (buckets) {
-          if (G.guard) BH_SPLIT(true, true, !kRaw); else BH_SPLIT(false, true, !kRaw);
-        } else {
-          if (G.guard) BH_SPLIT(true, false, !kRaw); else BH_SPLIT(false, false, !kRaw);
-        }
+#define BH_SPLIT(guard_, bucket_) \
+  split_cluster<kF64, kMode, kSoft, kGroupTheta, guard_, bucket_, kOff32>(a, wn, C, k, r0, r1, runs, mine, w, &ticket, part)
+      if (buckets) {
+        if (G.guard) BH_SPLIT(true, true); else BH_SPLIT(false, true);
       } else {
-        // (trees this large have only the branchless guard and bucket variant)
-        BH_SPLIT(true, true, false);
+        if (G.guard) BH_SPLIT(true, false); else BH_SPLIT(false, false);
       }
 #undef BH_SPLIT
     }

@@ -270,13 +270,16 @@ hipError_t ensure_target_order(const bh_tree* t, hipStream_t st) {
 // fill the chip by themselves, and waves waiting for the last run of their group
 // cost more than they bring (clumpy 200,003: 659, 973 with 4).  A forest's clusters
 // may have the most runs, whose sums leave a CU LDS for two workgroups: 16 waves
-// (20 clusters, 56,000 particles: 508, 285, 182, 139).  The registers of walks of
-// order 2 hold one workgroup of 16 waves per CU.
+// (4, 8 and 16: 20 clusters, 56,000 particles 213, 140, 104; 1000 clusters of 1 to
+// 100 particles 80, 61, 55), and 8 for order 2, whose registers hold one workgroup
+// of 16 waves per CU (273, 183, 203 and 91, 68, 84; FP64 30 clusters, 90,000
+// particles 445, 306, 343).
 int split_waves(int64_t n, int64_t n_seg, int order) {
   const int64_t groups = (n + 63) / 64;
   if (n > bh::kSplitMaxN) return 1;
-  if (groups <= 256 || n_seg > 1) return 16;
-  return groups <= 512 ? (order == 2 ? 8 : 16) : 4;
+  if (groups <= 256) return 16;
+  if (groups <= 512 || n_seg > 1) return order == 2 ? 8 : 16;
+  return 4;
 }
 
 int run_walk(const bh_tree* t, double theta, const float* theta_group, double eps, void* acc, void* pot,

@@ -620,14 +620,16 @@ __device__ __forceinline__ void fold_run(Cursor<kF64, kT>& C, Totals<kT> tot, in
 // other clusters stay idle (skip past the subtree).
 // kRuns: some cluster's subtree is cut into several runs (else each cluster is
 // one run, and its sums stay in the accumulators).
-template <bool kF64, int kT, int kMode, bool kSoft, bool kPlain, bool kGuard, bool kBucket, bool kLds, bool kRuns>
+// kBig: the walk copy may hold more than 4 GiB.
+template <bool kF64, int kT, int kMode, bool kSoft, bool kPlain, bool kGuard, bool kBucket, bool kLds, bool kRuns,
+          bool kBig = true>
 __device__ __forceinline__ void walk_clusters(const WalkArgs& a, StepNode<kF64, kPlain> wn, Cursor<kF64, kT>& C,
                                               uint4 (*pf)[8], Totals<kT> tot, const int (&kc)[kT], int klo, int khi) {
   const int cap = 2 * a.n;
   const int lane = __lane_id();
   // (the plain nodes of the FP64 per-group-theta walk keep 64-bit addressing)
   constexpr bool kRaw = kF64 && kPlain;
-  const bool off32 = !kRaw && a.n < kOff32MaxN;
+  const bool off32 = !kRaw && (!kBig || a.n < kOff32MaxN);
   for (int k = klo; k <= khi; ++k) {
     const int r0 = min(max(uniform(a.croot[k]), 0), cap);
     const int r1 = min(max(uniform(a.croot[k + 1]), r0), cap);
@@ -640,7 +642,7 @@ __device__ __forceinline__ void walk_clusters(const WalkArgs& a, StepNode<kF64, 
       if constexpr (kLds && (kMode & kWalkQuad) == 0)
         walk_loop_lds<kF64, kT, kMode, kSoft, kPlain, kGuard, kBucket>(a, wn, C, pf, end);
       else if (off32)
-        walk_loop_scalar<kF64, kT, kMode, kSoft, kPlain, kGuard, kBucket, true>(a, wn, C, end);
+        walk_loop_scalar<kF64, kT, kMode, kSoft, kPlain, kGuard, kBucket, !kRaw>(a, wn, C, end);
       else
         walk_loop_scalar<kF64, kT, kMode, kSoft, kPlain, kGuard, kBucket, false>(a, wn, C, end);
     };
@@ -904,6 +906,16 @@ __device__ __forceinline__ void split_cluster(const WalkArgs& a, StepNode<kF64, 
   }
 }
 
+// Of a group whose targets lie in several clusters, a small cluster is walked by
+// one wave, the waves taking such clusters in turn: sharing it costs three
+// barriers and the runs' sums, some 3.5 us, while a step of one wave takes 0.2.  The
+// more clusters there are for the waves, the larger they may be: up to
+// kAloneNodes nodes for each, or for each wave.  (1000 clusters, FP32, us with
+// one wave per group, every cluster shared, and now: of 1 particle 24, 233, 11;
+// of 4 34, 68, 10; of 16 34, 26, 18; of 1 to 100 72, 58, 55.  100 of 1 to 100 with
+// kAloneNodes = 4, 8, 12, 16, 32: 34, 30, 35, 36, 50.)
+constexpr int kAloneNodes = 8;
+
 // One workgroup per group of 64 targets (forces; one target per lane).  (Monopole
 // kernels are asked for 8 waves per SIMD, so that two workgroups of 16 fit a CU:
 // clumpy 30,000 took 328 us with one, 209 with two, at 16 runs.)
@@ -927,12 +939,38 @@ void k_walk_split(WalkArgs a) {
   // the others' copies are below 4 GiB in every tree whose groups are shared)
   constexpr bool kOff32 = !(kF64 && kGroupTheta);
   static_assert(kSplitMaxN < kOff32MaxN, "shared walks assume 32-bit record offsets");
-  for (int k = G.klo; k <= G.khi; ++k) {
-    const int cap = 2 * a.n;
+  const int cap = 2 * a.n;
+  int alone = 0, k0 = G.klo, dk = 1;
+  if (G.klo < G.khi) {
+    alone = kAloneNodes * min(G.khi - G.klo + 1, nw);
+    int most = T.i >= 0 ? a.croot[G.kc[0] + 1] - T.node0 : 0;
+    for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, 64));
+    if (uniform(most) <= alone) {  // none is shared: a wave need not pass the others' clusters
+      k0 += w;
+      dk = nw;
+    }
+  }
+  for (int k = k0; k <= G.khi; k += dk) {
     const int r0 = min(max(uniform(a.croot[k]), 0), cap);
     const int r1 = min(max(uniform(a.croot[k + 1]), r0), cap);
-    const int runs = cluster_runs(a, k);
     const bool mine = T.i >= 0 && G.kc[0] == k;
+    if (r1 - r0 <= alone) {
+      if ((k - G.klo) % nw != w) continue;
+      Totals<1> tot = reinterpret_cast<Totals<1>>(part + w);  // (free: the last shared cluster ended with a barrier)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) tot[0][c][lane] = 0.0;
+      // (the general variant for all: its two tests are nothing beside the loads' latency)
+      walk_clusters<kF64, 1, kMode, kSoft, kGroupTheta, true, true, false, true, false>(a, wn, C, nullptr, tot, G.kc, k, k);
+      if (mine) {
+        const int64_t o = a.perm[T.i];
+        reinterpret_cast<R*>(a.acc)[3 * o] = (R)tot[0][0][lane];
+        reinterpret_cast<R*>(a.acc)[3 * o + 1] = (R)tot[0][1][lane];
+        reinterpret_cast<R*>(a.acc)[3 * o + 2] = (R)tot[0][2][lane];
+        reinterpret_cast<R*>(a.pot)[o] = (R)tot[0][3][lane];
+      }
+      continue;
+    }
+    const int runs = cluster_runs(a, k);
     if (threadIdx.x == 0) ticket = nw;
     __syncthreads();
     if (r0 < r1) {

@@ -595,7 +595,8 @@ __device__ __forceinline__ void walk_loop_lds(const WalkArgs& a, StepNode<kF64, 
 // cluster alone, so one wave that walks the runs one after the other (below)
 // and several that share them (walk_split) give the same bits.
 __device__ __forceinline__ int run_length(int r0, int r1, int runs) { return max(1, (r1 - r0 + runs - 1) / runs); }
-__device__ __forceinline__ int cluster_runs(const WalkArgs& a, int k) {
+template <typename Args>
+__device__ __forceinline__ int cluster_runs(const Args& a, int k) {
   return min(uniform(walk_segments(a.cfirst[k + 1] - a.cfirst[k])), a.max_runs);
 }
 
@@ -616,6 +617,28 @@ __device__ __forceinline__ void fold_run(Cursor<kF64, kT>& C, Totals<kT> tot, in
   }
 }
 
+// Force walks of order 2: what is needed only outside the step loop.  The loop's
+// two sets of records take nearly all scalar registers there, and the compiler
+// would load every launch argument ahead of the loop and keep it, at the price of
+// scalars moved to and from vector lanes in each step: the arguments are read again
+// where they are used (every walk kernel has the one argument), and uniform values
+// wait in a vector register.  What the loop does need is pinned to scalar
+// registers, or the compiler would read it again in every step, and wait for it.
+// (A forest of 30 clusters of 30,000 3395 -> 3198 us.  Other walks have scalars to
+// spare and gain nothing.)
+template <int kMode>
+constexpr bool kLateArgs = kMode == (kWalkForces | kWalkQuad);
+__device__ __forceinline__ int aside(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+__device__ __forceinline__ const BH_CONST WalkArgs& late_args() {
+  const uint64_t p = (uint64_t)(uintptr_t)(const BH_CONST char*)__builtin_amdgcn_kernarg_segment_ptr();
+  const uint32_t lo = (uint32_t)uniform(aside((int)(uint32_t)p)), hi = (uint32_t)uniform(aside((int)(uint32_t)(p >> 32)));
+  return *(const BH_CONST WalkArgs*)(uintptr_t)((uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ void pin_args(WalkArgs& a) { asm volatile("" : "+s"(a.eps2)); }
+
 // The clusters klo..khi of a wave, one subtree after the other; targets of the
 // other clusters stay idle (skip past the subtree).
 // kRuns: some cluster's subtree is cut into several runs (else each cluster is
@@ -625,11 +648,39 @@ template <bool kF64, int kT, int kMode, bool kSoft, bool kPlain, bool kGuard, bo
           bool kBig = true>
 __device__ __forceinline__ void walk_clusters(const WalkArgs& a, StepNode<kF64, kPlain> wn, Cursor<kF64, kT>& C,
                                               uint4 (*pf)[8], Totals<kT> tot, const int (&kc)[kT], int klo, int khi) {
-  const int cap = 2 * a.n;
   const int lane = __lane_id();
   // (the plain nodes of the FP64 per-group-theta walk keep 64-bit addressing)
   constexpr bool kRaw = kF64 && kPlain;
   const bool off32 = !kRaw && (!kBig || a.n < kOff32MaxN);
+  auto loop = [&](int end) {
+    if constexpr (kLds && (kMode & kWalkQuad) == 0)
+      walk_loop_lds<kF64, kT, kMode, kSoft, kPlain, kGuard, kBucket>(a, wn, C, pf, end);
+    else if (off32)
+      walk_loop_scalar<kF64, kT, kMode, kSoft, kPlain, kGuard, kBucket, !kRaw>(a, wn, C, end);
+    else
+      walk_loop_scalar<kF64, kT, kMode, kSoft, kPlain, kGuard, kBucket, false>(a, wn, C, end);
+  };
+  if constexpr (kRuns && kBig && kLateArgs<kMode>) {
+    for (int kv = aside(klo), khv = aside(khi); uniform(kv) <= uniform(khv); kv = aside(kv + 1)) {
+      const BH_CONST WalkArgs& l = late_args();
+      const int k = uniform(kv), cap = 2 * l.n;
+      const int r0 = min(max(uniform(l.croot[k]), 0), cap);
+      const int r1 = min(max(uniform(l.croot[k + 1]), r0), cap);
+      const int len = aside(run_length(r0, r1, cluster_runs(l, k))), last = aside(r1);
+      C.c = r0;
+      C.k = C.kend = 0;
+#pragma unroll
+      for (int t = 0; t < kT; ++t) C.t[t].skip = (C.t[t].i >= 0 && kc[t] == k) ? r0 : 0x7fffffff;
+      for (int end = r0; C.c < uniform(last);) {
+        end = min(end + uniform(len), uniform(last));
+        if (C.c >= end) continue;
+        loop(end);
+        fold_run<kF64, kT>(C, tot, lane);
+      }
+    }
+    return;
+  }
+  const int cap = 2 * a.n;
   for (int k = klo; k <= khi; ++k) {
     const int r0 = min(max(uniform(a.croot[k]), 0), cap);
     const int r1 = min(max(uniform(a.croot[k + 1]), r0), cap);
@@ -638,14 +689,6 @@ __device__ __forceinline__ void walk_clusters(const WalkArgs& a, StepNode<kF64, 
 #pragma unroll
     for (int t = 0; t < kT; ++t) C.t[t].skip = (C.t[t].i >= 0 && kc[t] == k) ? r0 : 0x7fffffff;
     if (r0 >= r1) continue;
-    auto loop = [&](int end) {
-      if constexpr (kLds && (kMode & kWalkQuad) == 0)
-        walk_loop_lds<kF64, kT, kMode, kSoft, kPlain, kGuard, kBucket>(a, wn, C, pf, end);
-      else if (off32)
-        walk_loop_scalar<kF64, kT, kMode, kSoft, kPlain, kGuard, kBucket, !kRaw>(a, wn, C, end);
-      else
-        walk_loop_scalar<kF64, kT, kMode, kSoft, kPlain, kGuard, kBucket, false>(a, wn, C, end);
-    };
     if constexpr (!kRuns) {
       loop(r1);
     } else {
@@ -793,24 +836,30 @@ __device__ __forceinline__ void walk_group(const WalkArgs& a, int group, uint4 (
   }
 #undef BH_WALK
 
+  auto store = [&](const auto& l) {
 #pragma unroll
-  for (int t = 0; t < kT; ++t) {
-    const Target<kF64>& T = C.t[t];
-    if (T.i < 0) continue;
-    if (kStats && a.group_steps && lane == 0) a.group_steps[T.slot >> 6] = C.steps;
-    const int o = a.perm[T.i];
-    R* accp = reinterpret_cast<R*>(a.acc);
-    R* potp = reinterpret_cast<R*>(a.pot);
-    accp[3 * (int64_t)o] = (R)(kRuns ? tot[t][0][lane] : T.acc.ax);
-    accp[3 * (int64_t)o + 1] = (R)(kRuns ? tot[t][1][lane] : T.acc.ay);
-    accp[3 * (int64_t)o + 2] = (R)(kRuns ? tot[t][2][lane] : T.acc.az);
-    potp[o] = (R)(kRuns ? tot[t][3][lane] : T.acc.p);
-    if constexpr (kStats) {
-      a.counts[2 * (int64_t)o] = T.n_pp;
-      a.counts[2 * (int64_t)o + 1] = T.n_pc;
-      a.hash[o] = T.h;
+    for (int t = 0; t < kT; ++t) {
+      const Target<kF64>& T = C.t[t];
+      if (T.i < 0) continue;
+      if (kStats && l.group_steps && lane == 0) l.group_steps[T.slot >> 6] = C.steps;
+      const int o = l.perm[T.i];
+      R* accp = reinterpret_cast<R*>(l.acc);
+      R* potp = reinterpret_cast<R*>(l.pot);
+      accp[3 * (int64_t)o] = (R)(kRuns ? tot[t][0][lane] : T.acc.ax);
+      accp[3 * (int64_t)o + 1] = (R)(kRuns ? tot[t][1][lane] : T.acc.ay);
+      accp[3 * (int64_t)o + 2] = (R)(kRuns ? tot[t][2][lane] : T.acc.az);
+      potp[o] = (R)(kRuns ? tot[t][3][lane] : T.acc.p);
+      if constexpr (kStats) {
+        l.counts[2 * (int64_t)o] = T.n_pp;
+        l.counts[2 * (int64_t)o + 1] = T.n_pc;
+        l.hash[o] = T.h;
+      }
     }
-  }
+  };
+  if constexpr (kRuns && kLateArgs<kMode>)
+    store(late_args());
+  else
+    store(a);
 }
 
 // ---- several waves per group
@@ -1020,6 +1069,7 @@ template <bool kF64, int kT, int kMode, bool kSoft, bool kGroupTheta>
 __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(!kF64 && kT == 1 && kMode == kWalkForces ? 8 : 1)))
 void k_walk_runs(WalkArgs a) {
+  if constexpr (kLateArgs<kMode>) pin_args(a);
   __shared__ uint4 pf_lds[4][2][8];
   extern __shared__ double dyn_lds[];  // per wave: the totals of its targets
   const int wv = threadIdx.x >> 6;
@@ -1041,6 +1091,7 @@ template <bool kF64, int kT, int kMode, bool kSoft, bool kGroupTheta>
 __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(!kF64 && kT == 1 && kMode == kWalkForces && !kGroupTheta ? 8 : 1)))  // (not order 2)
 void k_walk_persistent(WalkArgs a) {
+  if constexpr (kLateArgs<kMode>) pin_args(a);
   __shared__ uint4 pf_lds[4][2][8];
   extern __shared__ double dyn_lds[];
   const int wv = threadIdx.x >> 6;

@@ -53,13 +53,19 @@ inline int n_super(int64_t n) { return (int)((n_chunks(n) + kSuperChunks - 1) / 
 // the waves better (the run next to a group's targets holds the most work); what
 // limits them is that the workgroups a CU needs at once keep their runs' sums, 2
 // KB each, in its LDS: two workgroups up to 32,768 particles, four up to 65,536,
-// seven up to 102,400.
+// seven up to 102,400; and that a run of few nodes costs a wave more to enter and
+// to leave than to walk (shared walks of 50, 100, 350, 700 and 1000 particles, us
+// with 36 runs, 16 and 8: 9.8, 9.6, 9.7; 12.6, 11.2, 13.2; 20.8, 19.1, -; 31.0,
+// 28.0, -; 31.5, 33.0, -; by one wave each, 1025 clusters of 50: 77.6, -, 70.1,
+// 5000 of 100: 135, 128, 124).
 constexpr int kMaxRuns = 36;           // (two workgroups of 36 runs fill the 160 KB of a CU)
 constexpr int kAncSlots = 24;          // ancestors of a run's first node, by level (kLevels of them used)
 constexpr int kAncClusters = 1024;     // forests of at most this many clusters keep the lists
 constexpr int kMaxSplitWaves = 16;     // waves that share a group
 constexpr int64_t kSplitMaxN = 102400; // largest tree whose groups are shared (1600 groups)
-__host__ __device__ inline int walk_segments(int64_t n) { return n <= 32768 ? 36 : n <= 65536 ? 18 : n <= kSplitMaxN ? 10 : 1; }
+__host__ __device__ inline int walk_segments(int64_t n) {
+  return n <= 64 ? 8 : n <= 768 ? 16 : n <= 32768 ? 36 : n <= 65536 ? 18 : n <= kSplitMaxN ? 10 : 1;
+}
 // Dynamic LDS of the one-wave-per-group walks: the totals of a wave's targets.
 inline size_t walk_lds(int waves_per_block, int targets_per_lane) {
   return (size_t)waves_per_block * targets_per_lane * 4 * kWave * sizeof(double);

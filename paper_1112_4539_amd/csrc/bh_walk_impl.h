@@ -967,8 +967,10 @@ constexpr int kAloneNodes = 8;
 
 // One workgroup per group of 64 targets (forces; one target per lane).  (Monopole
 // kernels are asked for 8 waves per SIMD, so that two workgroups of 16 fit a CU:
-// clumpy 30,000 took 328 us with one, 209 with two, at 16 runs.)
-template <bool kF64, int kMode, bool kSoft, bool kGroupTheta>
+// clumpy 30,000 took 328 us with one, 209 with two, at 16 runs.)  kForest: the
+// tree has more than one cluster; a single tree's kernel goes without the loop over
+// them and the path of a cluster walked alone.
+template <bool kF64, int kMode, bool kSoft, bool kGroupTheta, bool kForest>
 __global__ __launch_bounds__(kWave * kMaxSplitWaves)
 __attribute__((amdgpu_waves_per_eu(kMode == kWalkForces ? 8 : 4)))
 void k_walk_split(WalkArgs a) {
@@ -989,8 +991,9 @@ void k_walk_split(WalkArgs a) {
   constexpr bool kOff32 = !(kF64 && kGroupTheta);
   static_assert(kSplitMaxN < kOff32MaxN, "shared walks assume 32-bit record offsets");
   const int cap = 2 * a.n;
-  int alone = 0, k0 = G.klo, dk = 1;
-  if (G.klo < G.khi) {
+  int alone = 0, k0 = kForest ? G.klo : 0, dk = 1;
+  const int k1 = kForest ? G.khi : 0;
+  if (kForest && G.klo < G.khi) {
     alone = kAloneNodes * min(G.khi - G.klo + 1, nw);
     int most = T.i >= 0 ? a.croot[G.kc[0] + 1] - T.node0 : 0;
     for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, 64));
@@ -999,11 +1002,11 @@ void k_walk_split(WalkArgs a) {
       dk = nw;
     }
   }
-  for (int k = k0; k <= G.khi; k += dk) {
+  for (int k = k0; k <= k1; k += dk) {
     const int r0 = min(max(uniform(a.croot[k]), 0), cap);
     const int r1 = min(max(uniform(a.croot[k + 1]), r0), cap);
-    const bool mine = T.i >= 0 && G.kc[0] == k;
-    if (r1 - r0 <= alone) {
+    const bool mine = T.i >= 0 && (!kForest || G.kc[0] == k);
+    if (kForest && r1 - r0 <= alone) {
       if ((k - G.klo) % nw != w) continue;
       Totals<1> tot = reinterpret_cast<Totals<1>>(part + w);  // (free: the last shared cluster ended with a barrier)
 #pragma unroll
@@ -1111,9 +1114,12 @@ static hipError_t launch_t(const WalkArgs& a, hipStream_t st) {
   const int groups = (a.n + kT * kWave - 1) / (kT * kWave);
   if constexpr (kT == 1 && (kMode & 3) == kWalkForces) {
     if (a.split_waves > 1) {
-      k_walk_split<kF64, kMode, kSoft, kGroupTheta>
-          <<<groups, a.split_waves * kWave, a.max_runs * sizeof(double) * 4 * kWave, st>>>(a);
-      return hipGetLastError();
+      auto go = [&](auto kernel) {
+        kernel<<<groups, a.split_waves * kWave, a.max_runs * sizeof(double) * 4 * kWave, st>>>(a);
+        return hipGetLastError();
+      };
+      return a.n_seg > 1 ? go(k_walk_split<kF64, kMode, kSoft, kGroupTheta, true>)
+                         : go(k_walk_split<kF64, kMode, kSoft, kGroupTheta, false>);
     }
   }
   const int wpb = a.waves_per_block;

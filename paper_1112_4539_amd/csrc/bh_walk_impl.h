@@ -624,8 +624,10 @@ __device__ __forceinline__ void fold_run(Cursor<kF64, kT>& C, Totals<kT> tot, in
 // where they are used (every walk kernel has the one argument), and uniform values
 // wait in a vector register.  What the loop does need is pinned to scalar
 // registers, or the compiler would read it again in every step, and wait for it.
-// (A forest of 30 clusters of 30,000 3395 -> 3198 us.  Other walks have scalars to
-// spare and gain nothing.)
+// (A forest of 30 clusters of 30,000 3395 -> 3198 us.  Other walks by one wave have
+// scalars to spare and gain nothing; shared ones only read what their stores need
+// late, which their loops for leaves of several particles gain from: 4096
+// coincident particles in FP64 1979 -> 1848 us with the build.)
 template <int kMode>
 constexpr bool kLateArgs = kMode == (kWalkForces | kWalkQuad);
 __device__ __forceinline__ int aside(int x) {
@@ -1038,15 +1040,16 @@ void k_walk_split(WalkArgs a) {
     __syncthreads();
     // the runs' sums in order, one sum per wave
     if (mine) {
-      const int64_t o = a.perm[T.i];
+      const BH_CONST WalkArgs& l = late_args();
+      const int64_t o = l.perm[T.i];
       for (int c = w; c < 4; c += nw) {
         double v = 0.0;
         if (r0 < r1)
           for (int s = 0; s < runs; ++s) v += part[s][c][lane];
         if (c < 3)
-          reinterpret_cast<R*>(a.acc)[3 * o + c] = (R)v;
+          reinterpret_cast<R*>(l.acc)[3 * o + c] = (R)v;
         else
-          reinterpret_cast<R*>(a.pot)[o] = (R)v;
+          reinterpret_cast<R*>(l.pot)[o] = (R)v;
       }
     }
     __syncthreads();

@@ -634,10 +634,11 @@ __device__ __forceinline__ int aside(int x) {
   asm volatile("" : "+v"(x));
   return x;
 }
-__device__ __forceinline__ const BH_CONST WalkArgs& late_args() {
+template <typename Args = WalkArgs>
+__device__ __forceinline__ const BH_CONST Args& late_args() {
   const uint64_t p = (uint64_t)(uintptr_t)(const BH_CONST char*)__builtin_amdgcn_kernarg_segment_ptr();
   const uint32_t lo = (uint32_t)uniform(aside((int)(uint32_t)p)), hi = (uint32_t)uniform(aside((int)(uint32_t)(p >> 32)));
-  return *(const BH_CONST WalkArgs*)(uintptr_t)((uint64_t)hi << 32 | lo);
+  return *(const BH_CONST Args*)(uintptr_t)((uint64_t)hi << 32 | lo);
 }
 __device__ __forceinline__ void pin_args(WalkArgs& a) { asm volatile("" : "+s"(a.eps2)); }
 

@@ -389,8 +389,9 @@ BH_API int bh_mlp_adam(float *params, const float *grad, float *m, float *v, int
 /* Brute-force sum of Eq. (1) over all j != i for nt targets (Sec. 3):
  * pos [n][3], mass [n] device in precision prec; targets [nt] device int64
  * caller indices in [0, n); acc [nt][3], pot [nt] device outputs in target
- * order.  eps >= 0.  Terms are evaluated in the given precision and summed over
- * fixed ranges of j in ascending order (the ranges depend on n and nt only). */
+ * order.  eps >= 0.  Terms are evaluated in the given precision and summed in an
+ * order that depends on n and nt only: parts of the sources in the precision, each
+ * in ascending j, the parts' sums in FP64. */
 BH_API int bh_direct(const void *pos, const void *mass, int64_t n, int prec, const int64_t *targets,
               int64_t nt, double eps, void *acc, void *pot, void *stream);
 

@@ -117,9 +117,10 @@ __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirs
 
 // x^-1/2 in FP64 for x > 0: the hardware estimate y (relative error below
 // 2^-22) and one third-order step, y (1 - e)^-1/2 = y (1 + e/2 + 3/8 e^2 + ...)
-// with e = 1 - x y^2: the next term is below 2^-66, so what is left is the
-// rounding of x y (half an ulp of e, a quarter of the result's) and of the
-// last sum -- within 1 ulp, as 1/sqrt(x) with its two roundings is.  Six FP64
+// with e = 1 - x y^2.  |e| is below 2^-21, so the first term left out, 5/16 e^3,
+// is below 2^-64, and what remains is the rounding of x y (2^-53 of e, half of that
+// of the result: up to half an ulp) and of the last sum (half an ulp) -- within 1
+// ulp, as 1/sqrt(x) with its two roundings is.  Six FP64
 // instructions and the estimate, in place of about 35 for an IEEE square root
 // and a division.  x = inf gives 0 (there e is NaN, which the maximum drops).
 __device__ __forceinline__ double inv_sqrt_f64(double x) {

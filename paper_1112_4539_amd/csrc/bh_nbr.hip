@@ -323,7 +323,7 @@ __device__ void nbr_subtree(const NbrArgs& a, NbrTarget& T, int idx0, int c, int
 // (The arguments that the loops do not need are read again where they are used: a
 // batch of particles and two records leave no scalar registers to keep them in,
 // and the FP32 search with lists moved 18 scalars to and from vector lanes for
-// every batch.  Plummer 300,000, 32-entry lists 610 -> 529 us, without 504 -> 489.)
+// every batch.  Plummer 300,000, 32-entry lists 610 -> 529 us, without 504 -> 470.)
 template <bool kF64, bool kLists>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void k_nbr(NbrArgs a) {
   using T4 = typename std::conditional<kF64, double4, float4>::type;

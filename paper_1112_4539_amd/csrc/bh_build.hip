@@ -1580,7 +1580,7 @@ static hipError_t hilbert_impl(int n, const BuildWs& w, hipStream_t st) {
 // of it), a barrier where they have a launch.  It ends with the Hilbert walk
 // order.  As a sequence of kernels a small build is bound by its launches, some
 // 95 of about 4 us (340 us for 1000 particles, 390 us for 4096 in FP64); here it
-// is bound by the latency of one workgroup's steps: 82 and 142 us.  More
+// is bound by the latency of one workgroup's steps: 54 and 131 us.  More
 // particles do not fit the LDS.
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / kWave;

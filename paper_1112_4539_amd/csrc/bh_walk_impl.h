@@ -964,8 +964,8 @@ __device__ __forceinline__ void split_cluster(const WalkArgs& a, StepNode<kF64, 
 // more clusters there are for the waves, the larger they may be: up to
 // kAloneNodes nodes for each, or for each wave.  (1000 clusters, FP32, us with
 // one wave per group, every cluster shared, and now: of 1 particle 24, 233, 11;
-// of 4 34, 68, 10; of 16 34, 26, 18; of 1 to 100 72, 58, 55.  100 of 1 to 100 with
-// kAloneNodes = 4, 8, 12, 16, 32: 34, 30, 35, 36, 50.)
+// of 4 34, 68, 10; of 16 34, 26, 17; of 1 to 100 72, 58, 46.  100 of 1 to 100 with
+// kAloneNodes = 4, 8, 12, 16, 32, at 36 runs a cluster: 34, 30, 35, 36, 50.)
 constexpr int kAloneNodes = 8;
 
 // One workgroup per group of 64 targets (forces; one target per lane).  (Monopole

@@ -62,7 +62,14 @@ constexpr int kMaxRuns = 36;           // (two workgroups of 36 runs fill the 16
 constexpr int kAncSlots = 24;          // ancestors of a run's first node, by level (kLevels of them used)
 constexpr int kAncClusters = 1024;     // forests of at most this many clusters keep the lists
 constexpr int kMaxSplitWaves = 16;     // waves that share a group
-constexpr int64_t kSplitMaxN = 102400; // largest tree whose groups are shared (1600 groups)
+// Largest tree whose groups are shared (1600 groups).  Up to it every set measured
+// gains; beyond it sharing gains on centrally peaked sets only, and less and less
+// (walks by one wave per group and by four sharing it, at 10 runs, us: 102,401
+// particles Plummer 699 and 422, FP64 833 and 540, order 2 1104 and 775; clumpy 479
+// and 355, 553 and 425, 717 and 626; 131,072 Plummer 758 and 595, clumpy 557 and
+// 522, order 2 797 and 872; 150,000 804 and 686, 631 and 661; 200,000 864 and 872,
+// 660 and 806).
+constexpr int64_t kSplitMaxN = 102400;
 __host__ __device__ inline int walk_segments(int64_t n) {
   return n <= 64 ? 8 : n <= 768 ? 16 : n <= 32768 ? 36 : n <= 65536 ? 18 : n <= kSplitMaxN ? 10 : 1;
 }
